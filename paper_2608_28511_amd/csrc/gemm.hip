@@ -11,19 +11,22 @@
 //   KGRP mode   C_e[m, n] = sum_{r in segment e} A[r, m] * B[r, n]  (wgrad:
 //               the contraction runs over the expert's ragged rows).
 //
-// Two block tiles, chosen per launch (Tile below), on 512 threads: 8
-// wavefronts in a 2 x 4 grid, each (BM/2) x 64 outputs (v_mfma_f32_16x16x32_bf16):
-//   128 x 256, 64 k per stage, 3-stage ring of 48 KB stages;
-//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages -- one third
-//   fewer operand bytes per product, for launches long enough that the
-//   coarser tile count does not leave the last round of CUs half idle.
-// Neither the MFMAs nor copy bandwidth bound the kernel: the per-CU
-// texture-data return path reads 82% busy at 0.42 of the MFMA rate while a
-// plain stream of the same copies reaches ~4x these bytes per clock, so the
-// waits are on copy latency (a quarter of the operand reads miss L2); the
-// 256-row tile moves a third less per flop.  One workgroup fills a CU's LDS,
-// so each SIMD runs two wavefronts: one wave's address arithmetic, barrier
-// and LDS latency overlap the other's MFMAs.
+// Three block tiles on 512 threads, 8 wavefronts in a 2 x 4 grid
+// (v_mfma_f32_16x16x32_bf16):
+//   phased 256 x 256 (phased.h), 64 k per k tile: ROWS launches long enough
+//     that its coarser tile count does not cost a round (take_phased).  Its two
+//     groups of waves alternate between reading fragments and multiplying, so
+//     the matrix pipes are busy 80-90% of the k loop (the 128-row tile: 67%);
+//     under it the chip is power bound: 1.6-1.75 GHz at 1.2-1.36 PFLOP/s.
+//   128 x 256, 64 k per stage, 3-stage ring of 48 KB stages: the other ROWS
+//     launches and the shortest weight gradients;
+//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: weight gradients,
+//     and the products over an MX-FP8 A that are long enough.
+// For the last two neither the MFMAs nor copy bandwidth bound the kernel: all
+// eight waves read after each barrier and then all multiply, and the waits
+// are on LDS and copy latency.
+// One workgroup fills a CU's LDS, so each SIMD runs two wavefronts: one wave's
+// address arithmetic, barrier and LDS latency overlap the other's MFMAs.
 //
 // Operands never pass through registers on their way to LDS: every 16-byte
 // chunk is copied by a buffer load with an LDS destination into the LDS
@@ -78,6 +81,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "phased.h"
 #include "schedule.h"
 #include "tile_dma.h"
 
@@ -188,6 +192,8 @@ struct GemmArgs {
     const int32_t* mtile_total_l;
     const int32_t* a_perm;    // ROWS mode, bf16 A gathered: row r of the product is A row a_perm[r] / a_div
     int a_div;
+    uint32_t a_mul;           // v / a_div = v * a_mul >> a_shift for 0 <= v < 2^31
+    int a_shift;
     int64_t a_src_rows;       // rows of the gathered A
     const uint8_t* A_scale;   // MX-FP8 A: E8M0 scales [R, Kd / 32]
     uint32_t scale_bytes;     // R * Kd / 32 rounded up to a multiple of 4
@@ -597,6 +603,7 @@ __device__ __forceinline__ void staged_store(const f32x4 (&acc)[MI][4], void* C,
     const uint32_t wr = ep + (uint32_t)(r * 128 + (lane >> 4 & 1) * 8);
     const int rr0 = lane >> 3, c = lane & 7;
     const bool col_ok = cbase + c * 8 < N;
+    const uint32_t ld = (uint32_t)ldc;   // a tile's offsets stay below 2^31 (at most 256 rows of 65536)
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
 #pragma unroll
@@ -622,8 +629,8 @@ __device__ __forceinline__ void staged_store(const f32x4 (&acc)[MI][4], void* C,
         for (int q = 0; q < 2; ++q) {
             const int rr = q * 8 + rr0;
             const u32x4 v = *(const lds_u32x4*)(uintptr_t)(ep + (uint32_t)(rr * 128 + ((c ^ (rr & 7)) * 16)));
-            const int64_t row = i * 16 + rr;
-            const uint32_t off = (row < nrows && col_ok) ? (uint32_t)((row * ldc + cbase + c * 8) * 2) : kDropOffset;
+            const int row = i * 16 + rr;
+            const uint32_t off = (row < nrows && col_ok) ? ((uint32_t)row * ld + (uint32_t)cbase + c * 8) * 2 : kDropOffset;
             __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, 0);
         }
     }
@@ -641,11 +648,12 @@ __device__ __forceinline__ void drelu2_load(u32x2 (&uu)[MI][4], const uint16_t* 
     const __amdgpu_buffer_rsrc_t ru = rows_rsrc(aux_in, rbase, nrows, ldc);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int64_t row = i * 16 + (lane & 15);
+        const int row = i * 16 + (lane & 15);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t col = cbase + j * 16 + 4 * (lane >> 4);
-            const uint32_t off = (row < nrows && col < N) ? (uint32_t)((row * ldc + col) * 2) : kDropOffset;
+            const int col = (int)cbase + j * 16 + 4 * (lane >> 4);
+            const uint32_t off =
+                (row < nrows && col < N) ? ((uint32_t)row * (uint32_t)ldc + (uint32_t)col) * 2 : kDropOffset;
             uu[i][j] = __builtin_amdgcn_raw_buffer_load_b64(ru, off, 0, 0);
         }
     }
@@ -665,11 +673,12 @@ __device__ __forceinline__ void f32_store(const f32x4 (&acc)[MI][4], float* C, i
                                                                         0x00020000);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        const int64_t row = i * 16 + (lane & 15);
+        const int row = i * 16 + (lane & 15);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t col = cbase + j * 16 + 4 * (lane >> 4);
-            const uint32_t off = (row < rows && col < N) ? (uint32_t)((row * ldc + col) * 4) : kDropOffset;
+            const int col = (int)cbase + j * 16 + 4 * (lane >> 4);
+            const uint32_t off =
+                (row < rows && col < N) ? ((uint32_t)row * (uint32_t)ldc + (uint32_t)col) * 4 : kDropOffset;
             f32x4 v = acc[i][j];
             if (accumulate) {
                 const u32x4 o = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
@@ -776,7 +785,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
         // they complete (loads complete in order among themselves).
         wait_stage<T, kPerStage>(g, g_total);
         stage_barrier();
-        if constexpr (EPI == EPI_DRELU2 && MI <= 4)   // with taller tiles: loaded in the epilogue
+        if constexpr (EPI == EPI_DRELU2)
             if (kc == 0)
                 drelu2_load(uu, p.aux_in, p.ldc, p.N, cur.row0 + wm * (BM / 2),
                             cur.row_hi - (cur.row0 + wm * (BM / 2)), cur.n0 + wn * 64, lane);
@@ -792,7 +801,6 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
             const int nrows = cur.row_hi - rbase;
             const int cbase = cur.n0 + wn * 64;
             if constexpr (EPI == EPI_DRELU2) {
-                if constexpr (MI > 4) drelu2_load(uu, p.aux_in, p.ldc, p.N, rbase, nrows, cbase, lane);
                 staged_store<EPI, 0, MI>(acc, p.C, p.ldc, p.N, rbase, nrows, cbase, ep, lane, uu);
             } else if constexpr (EPI == EPI_F32) {
                 f32_store(acc, (float*)p.C, p.ldc, p.N, rbase, nrows, cbase, p.accumulate != 0, lane);
@@ -814,39 +822,289 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
     for (int g = 0; g < g_total; g += kStages) ring_round<kStages>(step, g, g_total);
 }
 
-// Relative time of one 256-row tile against two 128-row tiles: the tall tile
-// moves a third fewer operand bytes per product (measured 0.91 over the five
-// layer shapes' real routing counts).
-constexpr int kTallTileCostPct = 91;
+// rows_body on the phased 256 x 256 tile: the same work list over 256-row
+// tiles.  Around each output tile's k loop the two groups of waves fall into
+// step, and what both need to do then is done once, at the same time: writing
+// the tile (128 KB a CU, at 64 bytes a clock 2,048 of its ~3,900 clocks) and
+// preparing the tile after the next.  A tile switch inside the k loop costs no
+// memory latency: the workgroup's tiles are listed in LDS at the start, the
+// perm entries of a tile's gathered rows are copied to LDS two tiles ahead,
+// and its descriptors and row offsets are ready when its copies begin.  All
+// copies in flight have landed before the stores are issued, so the next k
+// tile waits for neither.  (Writing the tile in pieces during the memory parts
+// of the phases instead, where the other group multiplies, was slower: 1.77 ->
+// 1.87 ms on 24 experts x 4,779 rows, 2,688 -> 3,520, because the groups' pieces
+// then follow each other.)
+// Measured, phased / 128- and 256-row tiles of one barrier per stage, up and
+// down projection: 64 experts x 768 rows (2,048 -> 1,024) 237 / 285 and 214 /
+// 249 us; 256 uneven experts x 256 rows (2,048 -> 2,688) 855 / 986 and 790 /
+// 880; 512 x 704 (672 -> 1,856) 1,034 / 1,158 and 832 / 1,013; 192 x 597 (2,688 ->
+// 3,520) 1,983 / 2,290 and 1,881 / 2,231; 24 x 4,779 of the same 1,674 / 1,966 and
+// 1,600 / 1,935 (1.30 and 1.36 PFLOP/s).
+constexpr int kPermBytes = kWaves * 256;                                        // 64 entries per wave
+constexpr int kPermOff = TileP::kRingBytes + kEpiBytes;
+constexpr int kListOff = kPermOff + kPermBytes;
+constexpr int kListTiles = (160 * 1024 - kListOff) / (int)sizeof(RowsTile);     // 896
 
-// The tile height of a launch, from the m-tile counts of both heights: the
-// busiest XCD's rounds of each (ceil(m / 8) m-tiles times n_tiles items over
-// G / 8 workgroups), tall tiles when their rounds cost less.  Every
-// workgroup reads the same counts, so the whole grid takes the same body.
-__device__ __forceinline__ bool take_tall_tiles(int m_small, int m_tall, int n_tiles, int G) {
-    const int Gx = G / kXcds;
-    const int r_small = ((m_small + kXcds - 1) / kXcds * n_tiles + Gx - 1) / Gx;
-    const int r_tall = ((m_tall + kXcds - 1) / kXcds * n_tiles + Gx - 1) / Gx;
-    return 2 * r_tall * kTallTileCostPct < 100 * r_small;
+// v, opaque to the optimiser: what is derived from it is computed where it is
+// used instead of being held in registers over the k loop.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
-constexpr int kRowsSmemBytes =
-    (TileS::kRingBytes > TileL::kRingBytes ? TileS::kRingBytes : TileL::kRingBytes) + kEpiBytes;
+// Work item w as in rows_tile, in per-lane code.
+template <int BM>
+__device__ __forceinline__ RowsTile rows_tile_lane(const GemmArgs& p, const int4* tiles, int m_count, int w,
+                                                   int m_base) {
+    RowsTile t;
+    int mt, nt;
+    if (tiles != nullptr) {
+        const int q = m_base + w / p.n_tiles;
+        const int packed = tiles[q].w;
+        int a = packed >> 4, b = a + (packed & 15);
+        a = a > m_base ? a : m_base;
+        b = b < m_base + m_count ? b : m_base + m_count;
+        if (a > q || b <= q) { a = q; b = q + 1; }
+        const int s = b - a;
+        const int in = w - (a - m_base) * p.n_tiles;
+        mt = a + in % s;
+        nt = in / s;
+        nt = nt < p.n_tiles ? nt : p.n_tiles - 1;
+        const int4 e = tiles[mt];
+        t.e = e.x;
+        t.row0 = e.y;
+        t.row_hi = e.z;
+    } else {
+        const int width = kGroupM * p.n_tiles;
+        const int group = w / width;
+        const int first_m = group * kGroupM;
+        const int gsz = (m_count - first_m) < kGroupM ? (m_count - first_m) : kGroupM;
+        const int in = w - group * width;
+        mt = m_base + first_m + in % gsz;
+        nt = in / gsz;
+        t.e = 0;
+        t.row0 = mt * BM;
+        t.row_hi = (t.row0 + BM) < p.M ? (t.row0 + BM) : (int)p.M;
+    }
+    t.n0 = nt * BN;
+    return t;
+}
 
-// The ROWS launch: one body per tile height, chosen on the device from the
-// tile schedule's counts (known only after routing).  Products with k-major
-// weights (the dgrads) always take 128-row tiles: measured on the same five
-// shapes, the tall tile never won for them.
+// At least two k tiles (Kd > 64): tile jc + 1 is prepared before tile jc's
+// second-last k tile starts sending it.
+// Items lx + j * Gx of the XCD's m-tiles [m_base, m_base + m_count), 0 <= j < n_mine <= kListTiles.
 template <bool B_K, int EPI, bool KTAIL>
+__device__ __forceinline__ void rows_list_phased(const GemmArgs& p, char* smem, const int4* tiles, int m_base,
+                                                 int m_count, int lx, int Gx, int n_mine) {
+    constexpr int BM = TileP::BM;
+    const int tid = threadIdx.x, lane_ = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int nk = (p.Kd + TileP::KD - 1) / TileP::KD;
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+    const uint32_t ep = lds0 + TileP::kRingBytes + (uint32_t)wave * kEpiWaveBytes;
+    const uint32_t perm_lds = lds0 + kPermOff + (uint32_t)wave * 256u;
+    RowsTile* list = (RowsTile*)(smem + kListOff);
+    for (int j = tid; j < n_mine; j += kGemmThreads)
+        list[j] = rows_tile_lane<BM>(p, tiles, m_count, lx + j * Gx, m_base);
+    __syncthreads();
+    auto tile_at = [&](int j) {
+        const RowsTile t = list[j];
+        RowsTile u;
+        u.e = __builtin_amdgcn_readfirstlane(t.e);
+        u.row0 = __builtin_amdgcn_readfirstlane(t.row0);
+        u.row_hi = __builtin_amdgcn_readfirstlane(t.row_hi);
+        u.n0 = __builtin_amdgcn_readfirstlane(t.n0);
+        return u;
+    };
+
+    Phased<true, B_K, KTAIL> ph;
+    ph.wave = wave;
+    ph.bases(lds0, wm, wn, lane_);
+    ph.nkd = nk;
+    ph.k_len = p.Kd;
+
+    // Gathered A: lane l < 32 of a wave brings the perm entry of tile row
+    // 128 (l / 16) + 16 wave + l % 16, the rows whose chunks the wave copies.
+    const bool gather = !B_K && p.a_perm != nullptr;
+    auto fetch_perm = [&](const RowsTile& t) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the last entries are read
+        const int lane = fresh(lane_);
+        const uint32_t row = (uint32_t)((lane >> 4) * 128 + wave * 16 + (lane & 15));
+        const int n = t.row_hi - t.row0;
+        dma4(buf_rsrc(p.a_perm + t.row0, (uint32_t)(n > 0 ? n * 4 : 0)), lane < 32 ? row * 4u : kDmaDrop, perm_lds);
+    };
+    // nxt: the tile after the one being sent; its operands' descriptors and, with
+    // gathered rows, its chunks are prepared where both groups are in step.
+    // ahead: the tile after that one, whose perm entries are on their way.
+    using PH = Phased<true, B_K, KTAIL>;
+    struct Next {
+        i32x4 a, b;
+        int cols;
+        uint32_t off[2][2];
+    } nxt;
+    RowsTile cur = tile_at(0);
+    RowsTile ahead = cur;
+    auto prepare = [&]() {   // tile `ahead`, whose perm entries have landed
+        const RowsTile& t = ahead;
+        if (gather) {
+            const int lane = fresh(lane_);
+            nxt.a = buf_rsrc(p.A, (uint32_t)(p.a_src_rows * p.lda * 2));
+            PH::DA::gathered_chunks(nxt.off, p.lda, p.a_src_rows, lane, [&](int h, int i) {
+                const int r = h * 16 + i * 8 + (lane >> 3);
+                const int v = *(const __attribute__((address_space(3))) int*)(uintptr_t)(perm_lds + r * 4);
+                const bool in = t.row0 + h * 128 + (wave * 2 + i) * 8 + (lane >> 3) < t.row_hi;
+                const uint32_t tok = (uint32_t)(((uint64_t)(uint32_t)v * p.a_mul) >> p.a_shift);
+                return in && v >= 0 ? (int)tok : -1;
+            });
+        } else {
+            nxt.a = PH::DA::span(p.A, p.lda, t.row0, t.row_hi, 0, p.Kd);
+        }
+        nxt.b = PH::DB::span(p.B + (int64_t)t.e * p.b_stride, p.ldb, t.n0, p.N, 0, p.Kd);
+        nxt.cols = p.N - t.n0;
+    };
+    auto look_ahead = [&](int j) {
+        ahead = tile_at(j);
+        if (gather) fetch_perm(ahead);
+    };
+    auto take = [&]() {
+        const int lane = fresh(lane_);
+        ph.da.rs = nxt.a;
+        ph.db.rs = nxt.b;
+        ph.da.first_chunks(p.lda, 0, wave, lane);
+        if (gather) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) ph.da.off[h][i] = nxt.off[h][i];
+        }
+        ph.db.first_chunks(p.ldb, nxt.cols, wave, lane);
+    };
+    int jd = 0;
+    auto next_tile = [&]() {
+        if (++jd < n_mine) {
+            take();
+        } else {
+            ph.da.stop();
+            ph.db.stop();
+        }
+    };
+    look_ahead(0);
+    if (gather) wait_vmcnt<0>();
+    prepare();
+    take();
+    if (n_mine > 1) {
+        look_ahead(1);
+        if (gather) wait_vmcnt<0>();
+        prepare();
+        if (n_mine > 2) look_ahead(2);   // its perm entries land with the first k tiles' copies
+    }
+    ph.start(next_tile);
+
+    f32x4 acc0[4][4], acc1[4][4];
+    for (int jc = 0; jc < n_mine; ++jc) {
+        const int r0 = cur.row0 + wm * 64, cbase = cur.n0 + wn * 64;
+        // a wave whose 64 rows of a half, or whose columns, are all padding has no products there
+        const bool on0 = cbase < p.N && r0 < cur.row_hi, on1 = cbase < p.N && r0 + 128 < cur.row_hi;
+        zero_acc(acc0);
+        zero_acc(acc1);
+        if (wm == 1) asm volatile("s_barrier" ::: "memory");   // group 1 one barrier behind
+        if (on0 && on1) {
+            ph.template k_tile<true, true>(acc0, acc1, true, true, next_tile);
+            for (int kc = 1; kc < nk; ++kc) ph.template k_tile<true, false>(acc0, acc1, true, true, next_tile);
+        } else {
+            ph.template k_tile<false, true>(acc0, acc1, on0, on1, next_tile);
+            for (int kc = 1; kc < nk; ++kc) ph.template k_tile<false, false>(acc0, acc1, on0, on1, next_tile);
+        }
+        if (wm == 0) asm volatile("s_barrier" ::: "memory");   // in step again: both groups write at once
+        const int lane = fresh(lane_);
+        // tile jc + 2 (jc + 1 is being sent); its perm entries landed during this tile's second k tile
+        if (jc + 2 < n_mine) prepare();
+        wait_vmcnt<0>();   // the next k tile is a FRESH one
+        if (jc + 3 < n_mine) look_ahead(jc + 3);
+        auto leave = [&](const f32x4 (&acc)[4][4], int rbase) {
+            const int nrows = cur.row_hi - rbase;
+            if constexpr (EPI == EPI_DRELU2) {
+                u32x2 uu[4][4];
+                drelu2_load(uu, p.aux_in, p.ldc, p.N, rbase, nrows, cbase, lane);
+                staged_store<EPI, 0, 4>(acc, p.C, p.ldc, p.N, rbase, nrows, cbase, ep, lane, uu);
+            } else if constexpr (EPI == EPI_F32) {
+                f32_store(acc, (float*)p.C, p.ldc, p.N, rbase, nrows, cbase, p.accumulate != 0, lane);
+            } else {
+                staged_store<EPI, 0, 4>(acc, p.C, p.ldc, p.N, rbase, nrows, cbase, ep, lane);
+                if constexpr (EPI == EPI_RELU2)
+                    if (p.aux_out != nullptr)
+                        staged_store<EPI, 1, 4>(acc, p.aux_out, p.ldc, p.N, rbase, nrows, cbase, ep, lane);
+            }
+        };
+        if (on0) leave(acc0, r0);
+        if (on1) leave(acc1, r0 + 128);
+        if (jc + 1 < n_mine) cur = tile_at(jc + 1);
+    }
+    wait_vmcnt<0>();   // no copy into LDS outlives the workgroup
+}
+
+template <bool B_K, int EPI, bool KTAIL>
+__device__ __forceinline__ void rows_body_phased(const GemmArgs& p, char* smem, const int4* tiles, int m_total) {
+    const int Gx = gridDim.x / kXcds;   // the grid is a multiple of kXcds
+    const int xcd = (int)(blockIdx.x % kXcds), lx = (int)(blockIdx.x / kXcds);
+    const int m_base = (int)((int64_t)m_total * xcd / kXcds);
+    const int m_count = (int)((int64_t)m_total * (xcd + 1) / kXcds) - m_base;
+    const int n_work = m_count * p.n_tiles;
+    const int n_mine = lx < n_work ? (n_work - lx + Gx - 1) / Gx : 0;
+    for (int j0 = 0; j0 < n_mine; j0 += kListTiles) {
+        __syncthreads();   // the last list is no longer read
+        rows_list_phased<B_K, EPI, KTAIL>(p, smem, tiles, m_base, m_count, lx + j0 * Gx, Gx,
+                                          n_mine - j0 < kListTiles ? n_mine - j0 : kListTiles);
+    }
+}
+
+// Rounds of the busiest XCD: ceil(m / 8) m-tiles times n_tiles items over its
+// G / 8 workgroups.
+__host__ __device__ __forceinline__ int tile_rounds(int m_tiles, int n_tiles, int G) {
+    const int Gx = G / kXcds;
+    return ((m_tiles + kXcds - 1) / kXcds * n_tiles + Gx - 1) / Gx;
+}
+
+// The tile of a bf16 ROWS launch, from the m-tile counts of both heights
+// (every workgroup reads the same counts, so the whole grid takes the same
+// body): the phased 256-row tile when its rounds cost less than those of the
+// 128-row tile.  A phased round costs 1.3 (one round, the chip half idle) to
+// 1.6 (many rounds) of a 128-row one: measured against each other, phased /
+// 128-row, 2 : 1 rounds take 0.74-0.87 of the time, 5 : 3 0.90, 9 : 5 0.79, 3 : 2
+// 1.01-1.04, 1 : 1 1.02-1.3 (64 to 65,536 rows over 8 to 256 experts, and
+// dense products of 512 to 16,384 rows).
+constexpr int kPhasedRoundPct = 152;
+__host__ __device__ __forceinline__ bool take_phased(int m_small, int m_tall, int n_tiles, int G) {
+    return tile_rounds(m_tall, n_tiles, G) * kPhasedRoundPct < tile_rounds(m_small, n_tiles, G) * 100;
+}
+
+// MX-FP8 A: relative time of one 256-row tile against two 128-row tiles (a
+// third fewer operand bytes per product; measured 0.91 over the five layer
+// shapes' real routing counts).
+constexpr int kTallTileCostPct = 91;
+__device__ __forceinline__ bool take_tall_tiles(int m_small, int m_tall, int n_tiles, int G) {
+    return 2 * tile_rounds(m_tall, n_tiles, G) * kTallTileCostPct < 100 * tile_rounds(m_small, n_tiles, G);
+}
+
+constexpr int kRowsSmemBytes = 160 * 1024;
+static_assert(TileS::kRingBytes + kEpiBytes <= kRowsSmemBytes && kListOff < kRowsSmemBytes, "LDS budget");
+
+// The ROWS launch.  MAYBE: the launch may take the phased tile, which the
+// kernel decides from the tile schedule's counts (known only after routing);
+// without it the kernel holds the 128-row body alone (see maybe_phased).
+template <bool B_K, int EPI, bool KTAIL, bool MAYBE>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_rows_kernel(GemmArgs p) {
     __shared__ __attribute__((aligned(1024))) char smem[kRowsSmemBytes];
     typedef const __attribute__((address_space(4))) int32_t* cnt_ptr;
     // the table's count, never beyond the table (the builder caps it too)
     const int m_small = p.mtile_total != nullptr ? min(*(cnt_ptr)p.mtile_total, p.m_tiles) : p.m_tiles;
-    if constexpr (!B_K) {
+    if constexpr (MAYBE) {
         const int m_tall = p.mtile_total_l != nullptr ? min(*(cnt_ptr)p.mtile_total_l, p.m_tiles_l) : p.m_tiles_l;
-        if (take_tall_tiles(m_small, m_tall, p.n_tiles, (int)gridDim.x)) {
-            rows_body<TileL, B_K, EPI, KTAIL>(p, smem, p.tiles_l, m_tall);
+        if (take_phased(m_small, m_tall, p.n_tiles, (int)gridDim.x)) {
+            rows_body_phased<B_K, EPI, KTAIL>(p, smem, p.tiles_l, m_tall);
             return;
         }
     }
@@ -917,14 +1175,35 @@ static int64_t rows_grid(const GemmArgs& a) {
     return need < G ? need : G;
 }
 
+// Whether a ROWS launch can take the phased tile.  Dense rows: the rule itself.
+// Expert segments, whose counts the host does not know: not with a single
+// round of 128-row tiles, and not below 80 rows per expert, where routing
+// without strong skew leaves no expert over 128 rows and both heights the same
+// tiles.  Such launches are short, and the kernel with both bodies costs them
+// up to 1 us (18.0 against 17.6 us at 1,024 rows of 8 experts, 43.8 against 43.0
+// us at 1,024 rows of 64).  The phased body needs two k tiles.
+static bool maybe_phased(const GemmArgs& a, int64_t G) {
+    if (a.Kd <= TileP::KD) return false;
+    if (a.tiles == nullptr) return take_phased(a.m_tiles, a.m_tiles_l, a.n_tiles, (int)G);
+    return tile_rounds(a.m_tiles, a.n_tiles, (int)G) > 1 && a.R >= 80 * (int64_t)a.E;
+}
+
+template <bool B_K, int EPI, bool KTAIL>
+static void launch_rows_kernel(const GemmArgs& a, int64_t G, hipStream_t st) {
+    if (maybe_phased(a, G))
+        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, true>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, false>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+}
+
 template <bool B_K, int EPI>
 static hipError_t launch_rows(const GemmArgs& a, hipStream_t st) {
     const int64_t G = rows_grid(a);
     if (G == 0) return hipSuccess;
     if (a.Kd % TileS::KD != 0)
-        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, true>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+        launch_rows_kernel<B_K, EPI, true>(a, G, st);
     else
-        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, false>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+        launch_rows_kernel<B_K, EPI, false>(a, G, st);
     return launch_check(st);
 }
 
@@ -1007,6 +1286,11 @@ hipError_t launch_grouped_rows_gather(const moe_bf16* X, int64_t ldx, int64_t x_
     a.lda = ldx;
     a.a_perm = perm;
     a.a_div = div;
+    // s = 31 + ceil(log2 div), m = ceil(2^s / div): m * div - 2^s < div <= 2^(s - 31), so v * m >> s is exact
+    int sh = 31;
+    while (((int64_t)1 << (sh - 31)) < div) ++sh;
+    a.a_shift = sh;
+    a.a_mul = (uint32_t)((((uint64_t)1 << sh) + div - 1) / div);
     a.a_src_rows = x_rows;
     rows_args(a, B, ldb, b_stride, C, ldc, aux_out, sched, E, R, N, Kd);
     return launch_rows_epi(a, false, epi, st);
