@@ -591,7 +591,7 @@ int moe_combine_bwd(const moe_bf16* dy, const moe_bf16* y_disp, const float* p_d
 
 size_t moe_grouped_ffn_bwd_workspace_bytes(int32_t E, int64_t R, int32_t D, int32_t F) {
     if (E < 1 || E > kMaxE || R < 0 || R >= kMaxRows || !dim_ok(D) || !dim_ok(F)) return 0;
-    return align256((size_t)R * F * 2) + moe::gemm_schedule_bytes(E, R) + align256((size_t)E * 4);
+    return align256((size_t)R * F * 2) + moe::gemm_schedule_bytes(E, R) + align256(moe::expert_order_bytes(E));
 }
 
 int moe_grouped_ffn_bwd(const moe_bf16* x_disp, const moe_bf16* u_save, const moe_bf16* h,
@@ -608,7 +608,7 @@ int moe_grouped_ffn_bwd(const moe_bf16* x_disp, const moe_bf16* u_save, const mo
     MOE_TRY(need(dW2, (uint64_t)E * F * D * 4, 16));
     const size_t du_bytes = align256((size_t)R * F * 2);
     const size_t sched_bytes = moe::gemm_schedule_bytes(E, R);
-    const size_t wsn = du_bytes + sched_bytes + align256((size_t)E * 4);
+    const size_t wsn = du_bytes + sched_bytes + align256(moe::expert_order_bytes(E));
     if (ws == nullptr || ws_bytes < wsn) return MOE_ERR_WORKSPACE;
     MOE_TRY(opt(ws, 256));
     moe_bf16* du = (moe_bf16*)ws;

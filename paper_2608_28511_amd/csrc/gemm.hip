@@ -13,15 +13,16 @@
 //
 // Three block tiles on 512 threads, 8 wavefronts in a 2 x 4 grid
 // (v_mfma_f32_16x16x32_bf16):
-//   phased 256 x 256 (phased.h), 64 k per k tile: ROWS launches long enough
-//     that its coarser tile count does not cost a round (take_phased).  Its two
+//   phased 256 x 256 (phased.h), 64 k per k tile: ROWS launches and the experts'
+//     weight gradients, where its coarser tile count does not cost a round
+//     (take_phased).  Its two
 //     groups of waves alternate between reading fragments and multiplying, so
 //     the matrix pipes are busy 80-90% of the k loop (the 128-row tile: 67%);
 //     under it the chip is power bound: 1.6-1.75 GHz at 1.2-1.36 PFLOP/s.
 //   128 x 256, 64 k per stage, 3-stage ring of 48 KB stages: the other ROWS
 //     launches and the shortest weight gradients;
-//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: weight gradients,
-//     and the products over an MX-FP8 A that are long enough.
+//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: dense weight
+//     gradients, and the products over an MX-FP8 A that are long enough.
 // For the last two neither the MFMAs nor copy bandwidth bound the kernel: all
 // eight waves read after each barrier and then all multiply, and the waits
 // are on LDS and copy latency.
@@ -64,8 +65,8 @@
 // same ring and each lane decodes its fragment right before the MFMA, with a
 // result identical to decoding first (see MxDma and mx_frag).
 //
-// KGRP mode (weight gradients) runs one workgroup per (expert, m-tile,
-// n-tile) item, two m-tiles at a time across all n-tiles so that the items
+// KGRP mode (weight gradients) takes (expert, m-tile, n-tile) items, one per
+// workgroup or, on the phased tile, claimed by persistent workgroups, two m-tiles at a time across all n-tiles so that the items
 // an XCD runs together keep their operand rows in its L2, and writes its fp32
 // tile through LDS as whole 256-byte row pieces with non-temporal stores.
 //
@@ -348,6 +349,12 @@ struct KgItem {
     int r, q, in;   // slot, problem, item; r < 0: padding
 };
 
+// The expert order's buffer: E ranks, then one claim counter per XCD, each in
+// a 128-byte line of its own.
+constexpr int kClaimStride = 32;
+__host__ __device__ __forceinline__ int order_claims(int E) { return (E + kClaimStride - 1) / kClaimStride * kClaimStride; }
+size_t expert_order_bytes(int E) { return (size_t)(order_claims(E) + kXcds * kClaimStride) * 4; }
+
 // Slots whose expert holds more than R / 16 rows: a prefix of the order.
 __device__ __forceinline__ int heavy_slots(const GemmArgs& p) {
     typedef const __attribute__((address_space(4))) int32_t* cptr;
@@ -391,6 +398,17 @@ __device__ __forceinline__ KgItem kg_item(unsigned b, int E, int per0, int per1,
     return KgItem{r, q, in};
 }
 
+// Items of XCD x in kg_item's order, its padding after the last one left out.
+__device__ __forceinline__ int kg_count(int x, int E, int per0, int per1, int H) {
+    const int perm = per0 > per1 ? per0 : per1;
+    const int n_hc = (int)(((int64_t)H * (per0 + per1) + kKgChunk - 1) / kKgChunk);
+    const int nhx = n_hc > x ? (n_hc - x + kXcds - 1) / kXcds : 0;
+    const int xp = ((x - n_hc) % kXcds + kXcds) % kXcds;
+    const int units = 2 * (E - H), full = units / kXcds;
+    const int pos = (full & 1) ? kXcds - 1 - xp : xp;
+    return nhx * kKgChunk + (full + (pos < units % kXcds ? 1 : 0)) * perm;
+}
+
 // The pair launch's grid: every XCD's longest possible share (8 heavy slots).
 inline int64_t kg_grid(int E, int64_t per0, int64_t per1) {
     const int64_t per = per0 + per1, perm = per0 > per1 ? per0 : per1;
@@ -425,17 +443,49 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_kernel(GemmArgs p0
     kgrp_item<T>(p, e, it.in, smem);
 }
 
+// Two m-tiles at a time across all n-tiles: the ~32 items an XCD runs
+// together then share two m-tiles of A rows and a run of n-tiles of B
+// rows, which fit its L2 (all m-tiles at a time did not: the 31.5B
+// shape's wgrad 3286 -> ~3100 us; groups of 4 and 8 fell in between).
+constexpr int kKgM = 2;
+
+// fp32 store of a wave's MI x 16 rows x 64 columns from row rbase and column
+// cbase of C_e, through the wave's 4 KB LDS slice: per 16-row block 16 x 64 fp32
+// go there (16-byte chunk c of row r at c ^ r) and come back as whole
+// 256-byte row pieces, 4 rows per store instruction, written
+// non-temporally: the gradient is not read here, and full lines keep the
+// bypassing writes efficient while the operand rows stay in L2.
+template <int MI>
+__device__ __forceinline__ void kgrp_store(const f32x4 (&acc)[MI][4], const GemmArgs& p, int e, uint32_t ep, int rbase,
+                                           int cbase, int lane) {
+    const int r = lane & 15;
+    const int rq = lane >> 4, c = lane & 15;
+    const int ncol = cbase + c * 4;
+    float* const C = (float*)p.C + (int64_t)e * p.c_stride + ncol;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int ch = (j * 4 + (lane >> 4)) ^ r;
+            *(__attribute__((address_space(3))) f32x4*)(uintptr_t)(ep + (uint32_t)(r * 256 + ch * 16)) = acc[i][j];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int rr = q * 4 + rq;
+            const f32x4 v =
+                *(const __attribute__((address_space(3))) f32x4*)(uintptr_t)(ep + (uint32_t)(rr * 256 + ((c ^ rr) * 16)));
+            const int64_t m = rbase + i * 16 + rr;
+            if (m < p.M && ncol < p.N) __builtin_nontemporal_store(v, (f32x4*)(C + m * p.ldc));
+        }
+    }
+}
+
 // Item `in` (an m-tile, n-tile pair) of expert (or row chunk) e.
 template <class T>
 __device__ __forceinline__ void kgrp_item(const GemmArgs& p, int e, int in, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar LDS offsets
     const int wm = wave >> 2, wn = wave & 3;
-    // Two m-tiles at a time across all n-tiles: the ~32 items an XCD runs
-    // together then share two m-tiles of A rows and a run of n-tiles of B
-    // rows, which fit its L2 (all m-tiles at a time did not: the 31.5B
-    // shape's wgrad 3286 -> ~3100 us; groups of 4 and 8 fell in between).
-    constexpr int kKgM = 2;
     const int width = kKgM * p.n_tiles;
     const int grp = in / width, first_m = grp * kKgM;
     const int gsz = (p.m_tiles - first_m) < kKgM ? (p.m_tiles - first_m) : kKgM;
@@ -484,35 +534,8 @@ __device__ __forceinline__ void kgrp_item(const GemmArgs& p, int e, int in, char
         for (int kt = 0; kt < nk; kt += T::kStages) ring_round<T::kStages>(step, kt, nk);
     }
 
-    // Epilogue through LDS (the ring is free once every wave has passed the
-    // barrier): per 16-row block the wave's 16 x 64 fp32 go to its 4 KB
-    // slice (16-byte chunk c of row r at c ^ r) and come back as whole
-    // 256-byte row pieces, 4 rows per store instruction, written
-    // non-temporally: the gradient is not read here, and full lines keep the
-    // bypassing writes efficient while the operand rows stay in L2.
-    __syncthreads();
-    const int64_t c_base = (int64_t)e * p.c_stride;
-    const uint32_t ep = lds0 + (uint32_t)wave * 4096u;
-    const int r = lane & 15;
-    const int rq = lane >> 4, c = lane & 15;
-    const int64_t ncol = n0 + wn * 64 + c * 4;
-#pragma unroll
-    for (int i = 0; i < T::MI; ++i) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int ch = (j * 4 + (lane >> 4)) ^ r;
-            *(__attribute__((address_space(3))) f32x4*)(uintptr_t)(ep + (uint32_t)(r * 256 + ch * 16)) = acc[i][j];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int rr = q * 4 + rq;
-            const f32x4 v =
-                *(const __attribute__((address_space(3))) f32x4*)(uintptr_t)(ep + (uint32_t)(rr * 256 + ((c ^ rr) * 16)));
-            const int64_t m = row0 + wm * (T::BM / 2) + i * 16 + rr;
-            if (m < row_hi && ncol < p.N)
-                __builtin_nontemporal_store(v, (f32x4*)((float*)p.C + c_base + m * p.ldc + ncol));
-        }
-    }
+    __syncthreads();   // the ring is free
+    kgrp_store<T::MI>(acc, p, e, lds0 + (uint32_t)wave * 4096u, (int)row0 + wm * (T::BM / 2), (int)n0 + wn * 64, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -586,6 +609,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, in
 }
 
 constexpr uint32_t kDropOffset = 0x80000000u;  // beyond any descriptor's range
+constexpr int kNonTemporal = 2;                // cache policy of a buffer store
 
 // Staged epilogue of one 64 x 64 wave tile (EPI_BF16 / EPI_RELU2 /
 // EPI_DRELU2): per 16-row block, the accumulators go to the wave's LDS slice
@@ -1061,6 +1085,182 @@ __device__ __forceinline__ void rows_body_phased(const GemmArgs& p, char* smem, 
     }
 }
 
+// fp32 store of a wave's 64 rows x 64 columns from row rbase and column cbase
+// of C_e through 2 KB of LDS: 16 rows x 32 columns at a time (16-byte chunk c
+// of row r at c ^ (r & 7)), read back as whole 128-byte row pieces and written
+// non-temporally, 8 rows per instruction (see kgrp_store).
+__device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], const GemmArgs& p, int e, uint32_t ep,
+                                                int rbase, int cbase, int lane) {
+    const int rows = (int)p.M - rbase < 64 ? (int)p.M - rbase : 64;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((float*)p.C + (int64_t)e * p.c_stride + (int64_t)rbase * p.ldc), 0,
+        rows > 0 ? (int32_t)(rows * p.ldc * 4) : 0, 0x00020000);
+    const int r = lane & 15, rr0 = lane >> 3, c = lane & 7;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 4; jj += 2) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int ch = (j * 4 + (lane >> 4)) ^ (r & 7);
+                *(__attribute__((address_space(3))) f32x4*)(uintptr_t)(ep + (uint32_t)(r * 128 + ch * 16)) =
+                    acc[i][jj + j];
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int rr = q * 8 + rr0;
+                const u32x4 v = *(const lds_u32x4*)(uintptr_t)(ep + (uint32_t)(rr * 128 + ((c ^ (rr & 7)) * 16)));
+                const int row = i * 16 + rr, col = cbase + jj * 16 + c * 4;
+                const uint32_t off =
+                    (row < rows && col < p.N) ? ((uint32_t)row * (uint32_t)p.ldc + (uint32_t)col) * 4 : kDropOffset;
+                __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kNonTemporal);
+            }
+        }
+}
+
+constexpr int kKgTabOff = TileP::kRingBytes + kWaves * 2048;
+constexpr int kKgMaxE = 1024;
+constexpr int kKgSlotOff = kKgTabOff + 3 * kKgMaxE * 4;
+static_assert(kKgSlotOff + 4 * 32 <= 160 * 1024, "LDS budget");
+
+// The pair launch on the phased tile, one workgroup per CU that runs items of
+// its XCD's order until none is left: its first two by position, then each
+// claimed from the XCD's counter while an earlier item is written.  The copies
+// of the next item start during the last two k tiles of the current one, so
+// neither a workgroup launch nor a cold pipeline stands between items, and an
+// item's stores drain under the next one's first k tile.  The matrix pipes are
+// busy 72% of the launch at 24 experts x 4,779 rows (2,688 x 3,520), against
+// 79-83% of the row products: both operands take two LDS transpose reads a
+// fragment.  Measured there, this / one 256-row item a workgroup and one barrier
+// a stage: 3,530 / 3,820 us; 128 Zipf-loaded experts x 1,024 rows (2,048 x
+// 1,024) 1,130-1,180 / 1,230.
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(GemmArgs p0, GemmArgs p1,
+                                                                            int32_t* __restrict__ claims) {
+    __shared__ __attribute__((aligned(1024))) char smem[160 * 1024];
+    const int tid = threadIdx.x, lane_ = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+    const uint32_t ep = lds0 + TileP::kRingBytes + (uint32_t)wave * 2048u;
+    int32_t* const tab_e = (int32_t*)(smem + kKgTabOff);      // per slot of the expert order: expert,
+    int32_t* const tab_k = tab_e + kKgMaxE;                   // first row,
+    int32_t* const tab_n = tab_k + kKgMaxE;                   // row count
+    struct Slot {
+        int q, e, k_begin, k_len, row0, n0;   // q < 0: no item; e < 0: padding of the order
+    };
+    Slot* const slots = (Slot*)(smem + kKgSlotOff);
+
+    const int E = p0.E, R = (int)p0.R;
+    for (int r = tid; r < E; r += kGemmThreads) {
+        int e = p0.order[r];
+        e = (e >= 0 && e < E) ? e : r;
+        int lo = p0.offsets[e], hi = p0.offsets[e + 1];
+        lo = lo < 0 ? 0 : (lo > R ? R : lo);
+        hi = hi < lo ? lo : (hi > R ? R : hi);
+        tab_e[r] = e;
+        tab_k[r] = lo;
+        tab_n[r] = hi - lo;
+    }
+    const int Gx = (int)gridDim.x / kXcds, x = (int)(blockIdx.x % kXcds), lx = (int)(blockIdx.x / kXcds);
+    const int per0 = p0.m_tiles * p0.n_tiles, per1 = p1.m_tiles * p1.n_tiles;
+    const int H = heavy_slots(p0);
+    const int n_x = kg_count(x, E, per0, per1, H);
+    auto describe = [&](int j, int slot) {
+        Slot s{-1, -1, 0, 0, 0, 0};
+        if (j < n_x) {
+            const KgItem it = kg_item((unsigned)(j * kXcds + x), E, per0, per1, H);
+            s.q = 0;
+            if (it.r >= 0) {
+                const int n_tiles = it.q ? p1.n_tiles : p0.n_tiles, m_tiles = it.q ? p1.m_tiles : p0.m_tiles;
+                const int width = kKgM * n_tiles;
+                const int grp = it.in / width, first_m = grp * kKgM;
+                const int gsz = (m_tiles - first_m) < kKgM ? (m_tiles - first_m) : kKgM;
+                const int in2 = it.in - grp * width;
+                s = Slot{it.q, tab_e[it.r], tab_k[it.r], tab_n[it.r], (first_m + in2 % gsz) * TileP::BM,
+                         in2 / gsz * TileP::BN};
+            }
+        }
+        slots[slot] = s;
+    };
+    __syncthreads();
+    if (tid < 2) describe(tid * Gx + lx, tid);
+    __syncthreads();
+    auto item = [&](int j) {
+        const Slot s = slots[j & 3];
+        Slot u;
+        u.q = __builtin_amdgcn_readfirstlane(s.q);
+        u.e = __builtin_amdgcn_readfirstlane(s.e);
+        u.k_begin = __builtin_amdgcn_readfirstlane(s.k_begin);
+        u.k_len = __builtin_amdgcn_readfirstlane(s.k_len);
+        u.row0 = __builtin_amdgcn_readfirstlane(s.row0);
+        u.n0 = __builtin_amdgcn_readfirstlane(s.n0);
+        return u;
+    };
+    // at least two k tiles, so that the copies run at most one item ahead
+    auto k_tiles = [](int len) { return len > TileP::KD ? (len + TileP::KD - 1) / TileP::KD : 2; };
+
+    using PH = Phased<false, false, false>;
+    PH ph;
+    ph.wave = wave;
+    ph.bases(lds0, wm, wn, lane_);
+    ph.k_len = 0;   // column-contiguous operands: the descriptors end the contraction
+    int jd = 0;
+    auto take = [&](const Slot& s) {
+        const int lane = fresh(lane_);
+        const GemmArgs& p = s.q > 0 ? p1 : p0;
+        const int M = s.e < 0 ? 0 : (int)p.M;
+        ph.da.rs = PH::DA::span(p.A, p.lda, s.row0, M, s.k_begin, s.k_begin + s.k_len);
+        ph.db.rs = PH::DB::span(p.B, p.ldb, s.n0, p.N, s.k_begin, s.k_begin + s.k_len);
+        ph.da.first_chunks(p.lda, M - s.row0, wave, lane);
+        ph.db.first_chunks(p.ldb, p.N - s.n0, wave, lane);
+        ph.nkd = k_tiles(s.k_len);
+    };
+    auto next_tile = [&]() {
+        const Slot s = item(++jd);
+        if (s.q >= 0) {
+            take(s);
+        } else {
+            ph.da.stop();
+            ph.db.stop();
+        }
+    };
+    Slot cur = item(0);
+    if (cur.q < 0) return;
+    take(cur);
+    ph.start(next_tile);
+
+    f32x4 acc0[4][4], acc1[4][4];
+    for (int jc = 0;; ++jc) {
+        const GemmArgs& p = cur.q > 0 ? p1 : p0;
+        const int M = cur.e < 0 ? 0 : (int)p.M;
+        const int r0 = cur.row0 + wm * 64, cbase = cur.n0 + wn * 64;
+        const bool on0 = cbase < p.N && r0 < M, on1 = cbase < p.N && r0 + 128 < M;
+        const int nk = k_tiles(cur.k_len);
+        zero_acc(acc0);
+        zero_acc(acc1);
+        if (wm == 1) asm volatile("s_barrier" ::: "memory");   // group 1 one barrier behind
+        if (on0 && on1) {
+            ph.k_tile<true, true>(acc0, acc1, true, true, next_tile);
+            for (int kc = 1; kc < nk; ++kc) ph.k_tile<true, false>(acc0, acc1, true, true, next_tile);
+        } else {
+            ph.k_tile<false, true>(acc0, acc1, on0, on1, next_tile);
+            for (int kc = 1; kc < nk; ++kc) ph.k_tile<false, false>(acc0, acc1, on0, on1, next_tile);
+        }
+        if (wm == 0) asm volatile("s_barrier" ::: "memory");   // in step again: both groups write at once
+        wait_vmcnt<0>();   // the next k tile is a FRESH one
+        const Slot nxt = item(jc + 1);
+        int claim = 0;
+        if (nxt.q >= 0 && tid == 0) claim = atomicAdd(claims + kClaimStride * x, 1);
+        const int lane = fresh(lane_);
+        if (on0) kgrp_store_half(acc0, p, cur.e, ep, r0, cbase, lane);
+        if (on1) kgrp_store_half(acc1, p, cur.e, ep, r0 + 128, cbase, lane);
+        if (nxt.q < 0) break;
+        if (tid == 0) describe(2 * Gx + claim, (jc + 2) & 3);
+        cur = nxt;
+    }
+    wait_vmcnt<0>();   // no copy into LDS outlives the workgroup
+}
+
 // Rounds of the busiest XCD: ceil(m / 8) m-tiles times n_tiles items over its
 // G / 8 workgroups.
 __host__ __device__ __forceinline__ int tile_rounds(int m_tiles, int n_tiles, int G) {
@@ -1350,24 +1550,31 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
     float* Cs[2] = {C0, C1};
     const int64_t lda[2] = {lda0, lda1}, ldb[2] = {ldb0, ldb1}, ldc[2] = {ldc0, ldc1}, cs[2] = {c_stride0, c_stride1};
     const int Ms[2] = {M0, M1}, Ns[2] = {N0, N1};
-    int64_t items_l = 0;
+    int64_t items[2] = {0, 0};   // of 128-row and of 256-row tiles
     for (int q = 0; q < 2; ++q) {
         a[q].A = As[q]; a[q].B = Bs[q]; a[q].C = Cs[q]; a[q].offsets = offsets; a[q].order = order;
         a[q].lda = lda[q]; a[q].ldb = ldb[q]; a[q].ldc = ldc[q]; a[q].c_stride = cs[q];
         a[q].M = Ms[q]; a[q].R = R; a[q].N = Ns[q]; a[q].E = E;
-        items_l += (int64_t)E * ((Ms[q] + TileL::BM - 1) / TileL::BM) * ((Ns[q] + BN - 1) / BN);
+        for (int h = 0; h < 2; ++h)
+            items[h] += (int64_t)E * ((Ms[q] + kSchedBM[h] - 1) / kSchedBM[h]) * ((Ns[q] + BN - 1) / BN);
     }
-    // tall tiles when both gradients have enough items to fill the device a few times over
-    const bool large = items_l >= 4 * persistent_grid();
+    // The phased tile when its rounds of items over the device cost less, as in
+    // take_phased.  Measured, phased / 128-row: rounds 1 : 1 1.38 (32 items of 256
+    // rows), 1 : 2 0.85, 2 : 4 0.86-0.89, 4 : 8 0.83 (0.94-1.00 with 64 to 128 rows an
+    // expert, where the stores of the gradients take most of the time), 16 : 32
+    // 0.79-0.80, 32 : 64 of 32 rows an expert 0.94.
+    const int64_t G = persistent_grid();
+    const bool tall = (items[1] + G - 1) / G * kPhasedRoundPct < (items[0] + G - 1) / G * 100;
     for (int q = 0; q < 2; ++q) {
-        a[q].m_tiles = (int)((Ms[q] + (large ? TileL::BM : TileS::BM) - 1) / (large ? TileL::BM : TileS::BM));
+        a[q].m_tiles = (Ms[q] + kSchedBM[tall] - 1) / kSchedBM[tall];
         a[q].n_tiles = (Ns[q] + BN - 1) / BN;
     }
     const int64_t n_wg =
         kg_grid(E, (int64_t)a[0].m_tiles * a[0].n_tiles, (int64_t)a[1].m_tiles * a[1].n_tiles);
     if (n_wg > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if (large)
-        hipLaunchKernelGGL(gemm_kgrp2_kernel<TileL>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a[0], a[1]);
+    if (tall)
+        hipLaunchKernelGGL(gemm_kgrp2_phased_kernel, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0],
+                           a[1], const_cast<int32_t*>(order) + order_claims(E));
     else
         hipLaunchKernelGGL(gemm_kgrp2_kernel<TileS>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a[0], a[1]);
     return launch_check(st);
@@ -1385,11 +1592,13 @@ hipError_t launch_chunked_wgrad(const moe_bf16* A, int64_t lda, const moe_bf16* 
 }
 
 // Experts ranked by row count, most first (ties to the lower index):
-// order[rank] = e.  One workgroup; each thread counts, for its experts, the
+// order[rank] = e, and the pair launch's claim counters behind it, zeroed.
+// One workgroup; each thread counts, for its experts, the
 // experts that come before them.
 __global__ __launch_bounds__(1024) void expert_order_kernel(const int32_t* __restrict__ offsets, int E, int R,
                                                             int32_t* __restrict__ order) {
     __shared__ int32_t cnt[1024];
+    for (int i = threadIdx.x; i < kXcds * kClaimStride; i += 1024) order[order_claims(E) + i] = 0;
     for (int e = threadIdx.x; e < E; e += 1024) {
         int lo = offsets[e], hi = offsets[e + 1];
         lo = lo < 0 ? 0 : (lo > R ? R : lo);

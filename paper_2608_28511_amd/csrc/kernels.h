@@ -125,7 +125,9 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
                                  const moe_bf16* B1, int64_t ldb1, float* C1, int64_t ldc1, int64_t c_stride1, int M1,
                                  int N1, const int32_t* offsets, const int32_t* order, int E, int64_t R,
                                  hipStream_t st);
-// order[rank] = expert with the rank-th most rows of offsets[0..E] (ties to the lower index).
+// order[rank] = expert with the rank-th most rows of offsets[0..E] (ties to the lower index); the buffer, of
+// expert_order_bytes(E), also holds the claim counters that launch_grouped_wgrad2 uses up (zeroed here).
+size_t expert_order_bytes(int E);
 hipError_t launch_expert_order(const int32_t* offsets, int E, int64_t R, int32_t* order, hipStream_t st);
 
 }  // namespace moe

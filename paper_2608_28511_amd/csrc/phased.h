@@ -10,7 +10,8 @@
 // schedule in which all eight waves read and then all compute.
 //
 //   wave (wm, wn) of 2 x 4: rows {64 wm .. +63} of both 128-row halves of the
-//   tile, columns 64 wn .. +63; accumulators acc0 hold half 0, acc1 half 1.  Phases of k tile t (k0, k1: its 32-deep k steps):
+//   tile, columns 64 wn .. +63; accumulators acc0 hold half 0, acc1 half 1.
+//   Phases of k tile t (k0, k1: its 32-deep k steps):
 //     0: read A half 0 k0                      acc0 += A0 k0 * B k0
 //     1: read A half 0 k1, B k1                acc0 += A0 k1 * B k1
 //     2: read A half 1 k0                      acc1 += A1 k0 * B k0

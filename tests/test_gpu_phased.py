@@ -102,6 +102,36 @@ def test_backward_products(D, F):
         assert torch.equal(dW2[e], h[a:b].float().T @ dy[a:b].float())
 
 
+# rows per expert at and beside the edges of the 64-row k tiles, empty experts
+# among them, twice over for a device's worth of items (and, in the last, one
+# expert so busy that its items are cut across the XCDs)
+WGRAD = [0, 1, 2, 63, 64, 65, 100, 127, 128, 129, 191, 192, 193, 0, 320, 7]
+
+
+@pytest.mark.parametrize("D,F", [(504, 512), (1000, 264), (760, 504)])
+@pytest.mark.parametrize("heavy", [0, 4000])
+def test_weight_gradients(D, F, heavy):
+    """Both weight gradients on the phased tile: short, empty and busy contractions, cut widths."""
+    counts = WGRAD * 4 + [heavy]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    r = [_cdiv(len(counts) * sum(_cdiv(m, h) * _cdiv(n, 256) for m, n in ((F, D), (D, F))), cus) for h in (128, 256)]
+    if r[1] * 152 >= r[0] * 100:
+        pytest.skip("this device keeps 128-row tiles for the shape")
+    g = torch.Generator(device=DEV).manual_seed(D * 1000 + F)
+    R, E = sum(counts), len(counts)
+    off = _segments(counts)
+    W1, W2 = _ints(g, (E, D, F), 1), _ints(g, (E, F, D), 1)
+    dy = _ints(g, (R, D), 1) * (torch.rand((R, D), generator=g, device=DEV) < 0.05)
+    u, x, h = _ints(g, (R, F), 2), _ints(g, (R, D), 1), _ints(g, (R, F), 1)
+    for _ in range(2):   # a second call finds the first one's counters used up
+        _, dW1, dW2 = layer.grouped_ffn_bwd(x, u, h, dy, off, W1, W2)
+        du = (_product(dy, off, W2.transpose(1, 2)) * 2 * u.float().clamp(min=0)).to(torch.bfloat16)
+        o = off.tolist()
+        for e, (a, b) in enumerate(zip(o, o[1:])):
+            assert torch.equal(dW1[e], x[a:b].float().T @ du[a:b].float()), e
+            assert torch.equal(dW2[e], h[a:b].float().T @ dy[a:b].float()), e
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fp32_outputs(accumulate):
     """The shared expert's fp32 products, forward and (with an addend) backward."""
