@@ -682,7 +682,8 @@ int moe_router_bwd(const moe_bf16* x_r, const float* Wr, const int32_t* topk_idx
 
 size_t moe_latent_proj_bwd_workspace_bytes(int64_t M, int32_t Kd, int32_t N) {
     if (M < 0 || M >= kMaxRows || !dim_ok(Kd) || !dim_ok(N)) return 0;
-    return align256((size_t)moe::wgrad_chunks(M, Kd, N) * Kd * N * 4);
+    const size_t n = moe::dense_wgrad_ws_bytes(M, Kd, N, 0, 0);
+    return align256(n > 0 ? n : 1);   // 0 says that the shape is not valid
 }
 
 int moe_latent_proj_bwd(const moe_bf16* x_in, const moe_bf16* W, const moe_bf16* dout, int64_t M, int32_t Kd,
@@ -707,12 +708,7 @@ int moe_latent_proj_bwd(const moe_bf16* x_in, const moe_bf16* W, const moe_bf16*
                                          nullptr, 1, M, Kd, N, stream));
     }
     if (dW != nullptr) {
-        const int nch = moe::wgrad_chunks(M, Kd, N);
-        const int64_t kchunk = M > 0 ? (M + nch - 1) / nch : 1;
-        float* part = (float*)ws;
-        MOE_HIP(moe::launch_chunked_wgrad(x_in, Kd, dout, N, part, N, (int64_t)Kd * N, nch, kchunk, Kd, N, M,
-                                          stream));
-        MOE_HIP(moe::launch_sum_planes(part, nch, Kd, N, 1, N, dW, stream));
+        MOE_HIP(moe::launch_dense_wgrad2(x_in, dout, dW, Kd, N, nullptr, nullptr, nullptr, 0, 0, M, ws, stream));
     }
     return MOE_OK;
 }
@@ -836,8 +832,7 @@ int moe_shared_expert_fwd(const moe_bf16* x, const moe_bf16* Ws1, const moe_bf16
 }
 
 static size_t shared_bwd_ws(int64_t S, int32_t D, int32_t Fs) {
-    const int nch = moe::wgrad_chunks(S, D > Fs ? D : Fs, D > Fs ? Fs : D);
-    return align256((size_t)S * Fs * 2) + align256((size_t)nch * D * Fs * 4);
+    return align256((size_t)S * Fs * 2) + align256(moe::dense_wgrad_ws_bytes(S, Fs, D, D, Fs));
 }
 
 size_t moe_shared_expert_bwd_workspace_bytes(int64_t S, int32_t D, int32_t Fs) {
@@ -863,7 +858,6 @@ int moe_shared_expert_bwd(const moe_bf16* x, const moe_bf16* u_s, const moe_bf16
     if (ws == nullptr || ws_bytes < shared_bwd_ws(S, D, Fs)) return MOE_ERR_WORKSPACE;
     MOE_TRY(opt(ws, 256));
     moe_bf16* du = (moe_bf16*)ws;
-    float* part = (float*)((char*)ws + align256((size_t)S * Fs * 2));
     if (S > 0) {
         // du = (dy Ws2^T) * 2 max(u, 0): Ws2 [Fs, D] read D-contiguous per output column
         MOE_HIP(moe::launch_grouped_rows(dy, D, Ws2, D, 0, true, du, Fs, moe::EPI_DRELU2, u_s, nullptr, nullptr, 1,
@@ -874,13 +868,9 @@ int moe_shared_expert_bwd(const moe_bf16* x, const moe_bf16* u_s, const moe_bf16
                                              nullptr, 1, S, D, Fs, stream, accumulate_dx != 0));
         }
     }
-    const int nch = moe::wgrad_chunks(S, D > Fs ? D : Fs, D > Fs ? Fs : D);
-    const int64_t kchunk = S > 0 ? (S + nch - 1) / nch : 1;
-    // dWs2 [Fs, D] = h_s^T dy;  dWs1 [D, Fs] = x^T du  (the partial buffer is reused in stream order)
-    MOE_HIP(moe::launch_chunked_wgrad(h_s, Fs, dy, D, part, D, (int64_t)Fs * D, nch, kchunk, Fs, D, S, stream));
-    MOE_HIP(moe::launch_sum_planes(part, nch, Fs, D, 1, D, dWs2, stream));
-    MOE_HIP(moe::launch_chunked_wgrad(x, D, du, Fs, part, Fs, (int64_t)D * Fs, nch, kchunk, D, Fs, S, stream));
-    MOE_HIP(moe::launch_sum_planes(part, nch, D, Fs, 1, Fs, dWs1, stream));
+    // dWs2 [Fs, D] = h_s^T dy and dWs1 [D, Fs] = x^T du, in one launch
+    MOE_HIP(moe::launch_dense_wgrad2(h_s, dy, dWs2, Fs, D, x, du, dWs1, D, Fs, S,
+                                     (char*)ws + align256((size_t)S * Fs * 2), stream));
     return MOE_OK;
 }
 

@@ -13,16 +13,16 @@
 //
 // Three block tiles on 512 threads, 8 wavefronts in a 2 x 4 grid
 // (v_mfma_f32_16x16x32_bf16):
-//   phased 256 x 256 (phased.h), 64 k per k tile: ROWS launches and the experts'
-//     weight gradients, where its coarser tile count does not cost a round
-//     (take_phased).  Its two
+//   phased 256 x 256 (phased.h), 64 k per k tile: the dense weight gradients, and
+//     ROWS launches and the experts' weight gradients where its coarser tile
+//     count does not cost a round (take_phased).  Its two
 //     groups of waves alternate between reading fragments and multiplying, so
 //     the matrix pipes are busy 80-90% of the k loop (the 128-row tile: 67%);
 //     under it the chip is power bound: 1.6-1.75 GHz at 1.2-1.36 PFLOP/s.
 //   128 x 256, 64 k per stage, 3-stage ring of 48 KB stages: the other ROWS
 //     launches and the shortest weight gradients;
-//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: dense weight
-//     gradients, and the products over an MX-FP8 A that are long enough.
+//   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: the products over
+//     an MX-FP8 A that are long enough.
 // For the last two neither the MFMAs nor copy bandwidth bound the kernel: all
 // eight waves read after each barrier and then all multiply, and the waits
 // are on LDS and copy latency.
@@ -77,6 +77,7 @@
 // time across all n-tiles, and the items a round of workgroups processes
 // together on one XCD are consecutive, so they share A rows and expert
 // weights in that XCD's L2.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -201,7 +202,6 @@ struct GemmArgs {
     int64_t lda, ldb, ldc;
     int64_t b_stride;         // elements between experts' B (ROWS mode)
     int64_t c_stride;         // elements between experts' C (KGRP mode)
-    int64_t kchunk;           // KGRP mode without offsets: group e contracts rows [e*kchunk, (e+1)*kchunk)
     int64_t M;                // dense rows (ROWS, no offsets) or output rows (KGRP)
     int64_t R;                // rows of the activation buffers: segments are clamped to [0, R)
     int N, Kd, E;
@@ -416,19 +416,6 @@ inline int64_t kg_grid(int E, int64_t per0, int64_t per1) {
     return kXcds * ((n_hc + kXcds - 1) / kXcds * kKgChunk + (2 * (int64_t)E + kXcds - 1) / kXcds * perm);
 }
 
-// One launch: (row chunk, m-tile, n-tile) items, item `in` of chunk e.  Each
-// XCD takes a contiguous range of chunks, so a chunk's items run
-// consecutively on one XCD and share its rows in that XCD's L2.
-template <class T>
-__global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp_kernel(GemmArgs p) {
-    __shared__ __attribute__((aligned(1024))) char smem[T::kRingBytes];
-    const int per = p.m_tiles * p.n_tiles;
-    const int lid = xcd_remap(blockIdx.x, gridDim.x);
-    const int e = lid / per;
-    const int in = lid - e * per;
-    kgrp_item<T>(p, e, in, smem);
-}
-
 // Two weight gradients over the same expert segments in one launch, items
 // placed as above, so each gradient's long contractions overlap the other's
 // instead of each launch ending on its own tail.
@@ -480,7 +467,7 @@ __device__ __forceinline__ void kgrp_store(const f32x4 (&acc)[MI][4], const Gemm
     }
 }
 
-// Item `in` (an m-tile, n-tile pair) of expert (or row chunk) e.
+// Item `in` (an m-tile, n-tile pair) of expert e.
 template <class T>
 __device__ __forceinline__ void kgrp_item(const GemmArgs& p, int e, int in, char* smem) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -493,8 +480,7 @@ __device__ __forceinline__ void kgrp_item(const GemmArgs& p, int e, int in, char
     const int mt = first_m + in2 % gsz, nt = in2 / gsz;
     const int64_t row0 = (int64_t)mt * T::BM;
     const int64_t row_hi = (row0 + T::BM) < p.M ? (row0 + T::BM) : p.M;
-    int64_t k_begin = p.offsets != nullptr ? (int64_t)p.offsets[e] : (int64_t)e * p.kchunk;
-    int64_t k_end = p.offsets != nullptr ? (int64_t)p.offsets[e + 1] : k_begin + p.kchunk;
+    int64_t k_begin = p.offsets[e], k_end = p.offsets[e + 1];
     k_begin = k_begin < 0 ? 0 : (k_begin > p.R ? p.R : k_begin);
     k_end = k_end < k_begin ? k_begin : (k_end > p.R ? p.R : k_end);
     const int64_t n0 = (int64_t)nt * BN;
@@ -1085,16 +1071,16 @@ __device__ __forceinline__ void rows_body_phased(const GemmArgs& p, char* smem, 
     }
 }
 
-// fp32 store of a wave's 64 rows x 64 columns from row rbase and column cbase
-// of C_e through 2 KB of LDS: 16 rows x 32 columns at a time (16-byte chunk c
-// of row r at c ^ (r & 7)), read back as whole 128-byte row pieces and written
-// non-temporally, 8 rows per instruction (see kgrp_store).
-__device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], const GemmArgs& p, int e, uint32_t ep,
-                                                int rbase, int cbase, int lane) {
-    const int rows = (int)p.M - rbase < 64 ? (int)p.M - rbase : 64;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)((float*)p.C + (int64_t)e * p.c_stride + (int64_t)rbase * p.ldc), 0,
-        rows > 0 ? (int32_t)(rows * p.ldc * 4) : 0, 0x00020000);
+// fp32 store of a wave's 64 rows x 64 columns to C (its first row, ldc apart),
+// columns from cbase, through 2 KB of LDS: 16 rows x 32 columns at a time
+// (16-byte chunk c of row r at c ^ (r & 7)), read back as whole 128-byte row
+// pieces and written non-temporally, 8 rows per instruction (see kgrp_store).
+// Rows from `rows` and columns from N on are dropped.
+__device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], float* C, int64_t ldc, int rows, int N,
+                                                uint32_t ep, int cbase, int lane) {
+    rows = rows < 64 ? rows : 64;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)C, 0, rows > 0 ? (int32_t)(rows * ldc * 4) : 0, 0x00020000);
     const int r = lane & 15, rr0 = lane >> 3, c = lane & 7;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -1112,11 +1098,20 @@ __device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], const 
                 const u32x4 v = *(const lds_u32x4*)(uintptr_t)(ep + (uint32_t)(rr * 128 + ((c ^ (rr & 7)) * 16)));
                 const int row = i * 16 + rr, col = cbase + jj * 16 + c * 4;
                 const uint32_t off =
-                    (row < rows && col < p.N) ? ((uint32_t)row * (uint32_t)p.ldc + (uint32_t)col) * 4 : kDropOffset;
+                    (row < rows && col < N) ? ((uint32_t)row * (uint32_t)ldc + (uint32_t)col) * 4 : kDropOffset;
                 __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kNonTemporal);
             }
         }
 }
+
+// The items of dense weight gradients: `whole` tiles over all rows, then the
+// other tiles in `chunks` pieces of chunk_rows rows each (chunk-major, so that
+// what runs together shares operand rows), whose partial tiles tile_sum_kernel
+// adds in order.  items: all of them, pieces counted.
+struct DensePlan {
+    int whole, chunks, chunk_rows, items;
+};
+constexpr int kPieceElems = TileP::BM * TileP::BN;
 
 constexpr int kKgTabOff = TileP::kRingBytes + kWaves * 2048;
 constexpr int kKgMaxE = 1024;
@@ -1134,8 +1129,14 @@ static_assert(kKgSlotOff + 4 * 32 <= 160 * 1024, "LDS budget");
 // fragment.  Measured there, this / one 256-row item a workgroup and one barrier
 // a stage: 3,530 / 3,820 us; 128 Zipf-loaded experts x 1,024 rows (2,048 x
 // 1,024) 1,130-1,180 / 1,230.
+//
+// DENSE: the weight gradients of dense projections, all rows one segment.  The
+// items of a DensePlan follow each other over the grid, a round of every XCD's
+// workgroups taking consecutive ones.
+template <bool DENSE>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(GemmArgs p0, GemmArgs p1,
-                                                                            int32_t* __restrict__ claims) {
+                                                                            int32_t* __restrict__ claims,
+                                                                            DensePlan plan, float* __restrict__ part) {
     __shared__ __attribute__((aligned(1024))) char smem[160 * 1024];
     const int tid = threadIdx.x, lane_ = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1150,40 +1151,64 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
     };
     Slot* const slots = (Slot*)(smem + kKgSlotOff);
 
-    const int E = p0.E, R = (int)p0.R;
-    for (int r = tid; r < E; r += kGemmThreads) {
-        int e = p0.order[r];
-        e = (e >= 0 && e < E) ? e : r;
-        int lo = p0.offsets[e], hi = p0.offsets[e + 1];
-        lo = lo < 0 ? 0 : (lo > R ? R : lo);
-        hi = hi < lo ? lo : (hi > R ? R : hi);
-        tab_e[r] = e;
-        tab_k[r] = lo;
-        tab_n[r] = hi - lo;
-    }
     const int Gx = (int)gridDim.x / kXcds, x = (int)(blockIdx.x % kXcds), lx = (int)(blockIdx.x / kXcds);
+    const int E = p0.E, R = (int)p0.R;
     const int per0 = p0.m_tiles * p0.n_tiles, per1 = p1.m_tiles * p1.n_tiles;
-    const int H = heavy_slots(p0);
-    const int n_x = kg_count(x, E, per0, per1, H);
+    int H = 0, n_x = 0;
+    if constexpr (!DENSE) {
+        for (int r = tid; r < E; r += kGemmThreads) {
+            int e = p0.order[r];
+            e = (e >= 0 && e < E) ? e : r;
+            int lo = p0.offsets[e], hi = p0.offsets[e + 1];
+            lo = lo < 0 ? 0 : (lo > R ? R : lo);
+            hi = hi < lo ? lo : (hi > R ? R : hi);
+            tab_e[r] = e;
+            tab_k[r] = lo;
+            tab_n[r] = hi - lo;
+        }
+        H = heavy_slots(p0);
+        n_x = kg_count(x, E, per0, per1, H);
+    }
+    // item `in` of problem q: two m-tiles at a time across all n-tiles
+    auto place = [&](Slot& s, int q, int in) {
+        const int n_tiles = q ? p1.n_tiles : p0.n_tiles, m_tiles = q ? p1.m_tiles : p0.m_tiles;
+        const int width = kKgM * n_tiles;
+        const int grp = in / width, first_m = grp * kKgM;
+        const int gsz = (m_tiles - first_m) < kKgM ? (m_tiles - first_m) : kKgM;
+        const int in2 = in - grp * width;
+        s.q = q;
+        s.row0 = (first_m + in2 % gsz) * TileP::BM;
+        s.n0 = in2 / gsz * TileP::BN;
+    };
     auto describe = [&](int j, int slot) {
         Slot s{-1, -1, 0, 0, 0, 0};
-        if (j < n_x) {
+        if constexpr (DENSE) {
+            const int g = j * (int)gridDim.x + x * Gx + lx;
+            int in = g;
+            s.e = 0;   // 0: straight to C, else piece e - 1 of the partial tiles
+            s.k_len = R;
+            if (g >= plan.whole && plan.chunks > 1) {
+                const int tail = per0 + per1 - plan.whole, t = g - plan.whole, c = t / tail;
+                in = plan.whole + (t - c * tail);
+                s.e = 1 + (t - c * tail) * plan.chunks + c;
+                s.k_begin = c * plan.chunk_rows < R ? c * plan.chunk_rows : R;
+                s.k_len = R - s.k_begin < plan.chunk_rows ? R - s.k_begin : plan.chunk_rows;
+            }
+            if (g < plan.items) place(s, in >= per0 ? 1 : 0, in >= per0 ? in - per0 : in);
+        } else if (j < n_x) {
             const KgItem it = kg_item((unsigned)(j * kXcds + x), E, per0, per1, H);
             s.q = 0;
             if (it.r >= 0) {
-                const int n_tiles = it.q ? p1.n_tiles : p0.n_tiles, m_tiles = it.q ? p1.m_tiles : p0.m_tiles;
-                const int width = kKgM * n_tiles;
-                const int grp = it.in / width, first_m = grp * kKgM;
-                const int gsz = (m_tiles - first_m) < kKgM ? (m_tiles - first_m) : kKgM;
-                const int in2 = it.in - grp * width;
-                s = Slot{it.q, tab_e[it.r], tab_k[it.r], tab_n[it.r], (first_m + in2 % gsz) * TileP::BM,
-                         in2 / gsz * TileP::BN};
+                s.e = tab_e[it.r];
+                s.k_begin = tab_k[it.r];
+                s.k_len = tab_n[it.r];
+                place(s, it.q, it.in);
             }
         }
         slots[slot] = s;
     };
     __syncthreads();
-    if (tid < 2) describe(tid * Gx + lx, tid);
+    if (tid < 2) describe(DENSE ? tid : tid * Gx + lx, tid);
     __syncthreads();
     auto item = [&](int j) {
         const Slot s = slots[j & 3];
@@ -1249,13 +1274,24 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         if (wm == 0) asm volatile("s_barrier" ::: "memory");   // in step again: both groups write at once
         wait_vmcnt<0>();   // the next k tile is a FRESH one
         const Slot nxt = item(jc + 1);
-        int claim = 0;
-        if (nxt.q >= 0 && tid == 0) claim = atomicAdd(claims + kClaimStride * x, 1);
+        int next = jc + 2;
+        if constexpr (!DENSE)
+            if (nxt.q >= 0 && tid == 0) next = 2 * Gx + atomicAdd(claims + kClaimStride * x, 1);
         const int lane = fresh(lane_);
-        if (on0) kgrp_store_half(acc0, p, cur.e, ep, r0, cbase, lane);
-        if (on1) kgrp_store_half(acc1, p, cur.e, ep, r0 + 128, cbase, lane);
+        // C at row r0 and column c0 of the columns below
+        float* C = (float*)p.C + (int64_t)cur.e * p.c_stride + (int64_t)r0 * p.ldc;
+        int64_t ldc = p.ldc;
+        int c0 = 0;
+        if constexpr (DENSE)
+            if (cur.e > 0) {
+                C = part + (int64_t)(cur.e - 1) * kPieceElems + wm * 64 * TileP::BN;
+                ldc = TileP::BN;
+                c0 = cur.n0;
+            }
+        if (on0) kgrp_store_half(acc0, C, ldc, M - r0, p.N - c0, ep, cbase - c0, lane);
+        if (on1) kgrp_store_half(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N - c0, ep, cbase - c0, lane);
         if (nxt.q < 0) break;
-        if (tid == 0) describe(2 * Gx + claim, (jc + 2) & 3);
+        if (tid == 0) describe(next, (jc + 2) & 3);
         cur = nxt;
     }
     wait_vmcnt<0>();   // no copy into LDS outlives the workgroup
@@ -1516,24 +1552,6 @@ hipError_t launch_grouped_rows_mx(const uint8_t* Aq, const uint8_t* A_scale, con
 }
 
 
-// KGRP launches: tall tiles when there are enough workgroups to fill the
-// device a few times over.
-static hipError_t launch_kgrp(GemmArgs a, int64_t groups, hipStream_t st) {
-    const int64_t nt = (a.N + BN - 1) / BN;
-    const int64_t mt_l = (a.M + TileL::BM - 1) / TileL::BM;
-    const bool large = groups * mt_l * nt >= 2 * persistent_grid();
-    a.m_tiles = (int)(large ? mt_l : (a.M + TileS::BM - 1) / TileS::BM);
-    a.n_tiles = (int)nt;
-    const int64_t n_wg = groups * a.m_tiles * a.n_tiles;
-    if (n_wg <= 0) return hipSuccess;
-    if (n_wg > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if (large)
-        hipLaunchKernelGGL(gemm_kgrp_kernel<TileL>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL(gemm_kgrp_kernel<TileS>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a);
-    return launch_check(st);
-}
-
 // Both weight gradients of the expert FFN in one launch (gemm_kgrp2_kernel),
 // items of the experts with the most rows first.
 hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf16* B0, int64_t ldb0, float* C0,
@@ -1573,22 +1591,109 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
         kg_grid(E, (int64_t)a[0].m_tiles * a[0].n_tiles, (int64_t)a[1].m_tiles * a[1].n_tiles);
     if (n_wg > 0x7fffffff) return hipErrorInvalidConfiguration;
     if (tall)
-        hipLaunchKernelGGL(gemm_kgrp2_phased_kernel, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0],
-                           a[1], const_cast<int32_t*>(order) + order_claims(E));
+        hipLaunchKernelGGL(gemm_kgrp2_phased_kernel<false>, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0], a[1],
+                           const_cast<int32_t*>(order) + order_claims(E), DensePlan{}, (float*)nullptr);
     else
         hipLaunchKernelGGL(gemm_kgrp2_kernel<TileS>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a[0], a[1]);
     return launch_check(st);
 }
 
-hipError_t launch_chunked_wgrad(const moe_bf16* A, int64_t lda, const moe_bf16* B, int64_t ldb, float* C,
-                                int64_t ldc, int64_t c_stride, int nchunk, int64_t kchunk, int M, int N,
-                                int64_t R, hipStream_t st) {
-    GemmArgs a{};
-    a.A = A; a.B = B; a.C = C; a.offsets = nullptr; a.kchunk = kchunk;
-    a.lda = lda; a.ldb = ldb; a.ldc = ldc; a.c_stride = c_stride;
-    a.M = M; a.R = R; a.N = N; a.E = nchunk;
-    if (R * (lda > ldb ? lda : ldb) * 2 >= kMaxDmaBytes) return hipErrorInvalidValue;
-    return launch_kgrp(a, nchunk, st);
+// The plan of dense weight gradients of n tiles over R rows on the 256
+// workgroups of a device (a device of another size runs the same plan, so the
+// sums' order is the same): whole rounds of tiles over all rows, then the rest
+// cut into the number of pieces whose rounds take least.  In units of one k
+// tile (1.5 us): a piece costs its k tiles and 4 more (start, stores, the
+// workgroups' spread), the sum of the pieces 0.035 per partial tile read or
+// written (256 KB at 5 TB/s) and 2 for its launch.  A chunk has at least two k tiles, and
+// the pieces' partial tiles at most 128 MB.
+static DensePlan dense_plan(int64_t R, int64_t n) {
+    constexpr int64_t G = 256;
+    const int64_t nk = (R + TileP::KD - 1) / TileP::KD, tail = n % G;
+    DensePlan best{(int)(n - tail), 1, (int)R, (int)n};
+    double cost = 0;
+    for (int64_t c = 1; tail > 0 && (c == 1 || (tail * c <= 2 * G && 2 * c <= nk)); ++c) {
+        const int64_t per = (nk + c - 1) / c;
+        const double t = (double)((tail * c + G - 1) / G) * (double)(per + 4) +
+                         (c > 1 ? 0.035 * (double)(tail * (2 * c + 1)) + 2 : 0);
+        if (c == 1 || t < cost) {
+            cost = t;
+            best.chunks = (int)c;
+            best.chunk_rows = c > 1 ? (int)(per * TileP::KD) : (int)R;
+            best.items = (int)(n - tail + tail * c);
+        }
+    }
+    return best;
+}
+
+static int64_t dense_tiles(int M, int N) {
+    return (int64_t)((M + TileP::BM - 1) / TileP::BM) * ((N + TileP::BN - 1) / TileP::BN);
+}
+
+size_t dense_wgrad_ws_bytes(int64_t R, int M0, int N0, int M1, int N1) {
+    const DensePlan pl = dense_plan(R, dense_tiles(M0, N0) + dense_tiles(M1, N1));
+    return pl.chunks > 1 ? (size_t)(pl.items - pl.whole) * kPieceElems * 4 : 0;
+}
+
+// C tiles from `whole` on = the sum of their partial tiles, chunks ascending.
+// Bandwidth-bound: one thread adds four columns, one block four rows.
+__global__ __launch_bounds__(256) void tile_sum_kernel(GemmArgs p0, GemmArgs p1, DensePlan plan,
+                                                       const float* __restrict__ part) {
+    int in = plan.whole + (int)blockIdx.y;
+    const float* src = part + (int64_t)blockIdx.y * plan.chunks * kPieceElems;
+    const int per0 = p0.m_tiles * p0.n_tiles;
+    const GemmArgs& p = in >= per0 ? p1 : p0;
+    if (in >= per0) in -= per0;
+    const int width = kKgM * p.n_tiles;
+    const int grp = in / width, first_m = grp * kKgM;
+    const int gsz = (p.m_tiles - first_m) < kKgM ? (p.m_tiles - first_m) : kKgM;
+    const int in2 = in - grp * width;
+    const int row = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6), col = ((int)threadIdx.x & 63) * 4;
+    const int m = (first_m + in2 % gsz) * TileP::BM + row, n = in2 / gsz * TileP::BN + col;
+    if (m >= p.M || n >= p.N) return;
+    src += row * TileP::BN + col;
+    f32x4 s = *(const f32x4*)src;
+#pragma unroll 4
+    for (int c = 1; c < plan.chunks; ++c) {
+        const f32x4 v = *(const f32x4*)(src + (int64_t)c * kPieceElems);
+        s[0] += v[0]; s[1] += v[1]; s[2] += v[2]; s[3] += v[3];
+    }
+    float* dst = (float*)p.C + (int64_t)m * p.ldc + n;   // 4-byte aligned
+    dst[0] = s[0]; dst[1] = s[1]; dst[2] = s[2]; dst[3] = s[3];
+}
+
+// C_q [M_q, N_q] = A_q^T B_q over R rows, q = 0 and (M1 > 0) 1, in one launch and
+// the sum of the pieces.  One problem at a time left each with its own partly
+// empty last round, and equal chunks of all tiles wrote every tile twice or
+// more: both gradients of 16,384 rows (2,688 x 3,520) took 2 x (360 + 40) us in
+// 128-row tiles of two chunks, and take 546 + 12 (1.14 PFLOP/s) here; the router's
+// (2,688 x 576) took 83 + 21 in nine chunks, and take 60 + 12 + 5 with the planes' sum.
+hipError_t launch_dense_wgrad2(const moe_bf16* A0, const moe_bf16* B0, float* C0, int M0, int N0, const moe_bf16* A1,
+                               const moe_bf16* B1, float* C1, int M1, int N1, int64_t R, void* ws, hipStream_t st) {
+    const int widest = std::max(std::max(M0, N0), std::max(M1, N1));
+    if (R * widest * 2 >= kMaxDmaBytes) return hipErrorInvalidValue;
+    GemmArgs a[2] = {};
+    const moe_bf16* As[2] = {A0, A1};
+    const moe_bf16* Bs[2] = {B0, B1};
+    float* Cs[2] = {C0, C1};
+    const int Ms[2] = {M0, M1}, Ns[2] = {N0, N1};
+    for (int q = 0; q < 2; ++q) {
+        a[q].A = As[q]; a[q].B = Bs[q]; a[q].C = Cs[q];
+        a[q].lda = Ms[q]; a[q].ldb = Ns[q]; a[q].ldc = Ns[q];
+        a[q].M = Ms[q]; a[q].R = R; a[q].N = Ns[q];
+        a[q].m_tiles = (Ms[q] + TileP::BM - 1) / TileP::BM;
+        a[q].n_tiles = (Ns[q] + BN - 1) / BN;
+    }
+    const int64_t n = dense_tiles(M0, N0) + dense_tiles(M1, N1);
+    if (n == 0) return hipSuccess;
+    const DensePlan pl = dense_plan(R, n);
+    const int64_t G = std::min<int64_t>(persistent_grid(), (pl.items + kXcds - 1) / kXcds * kXcds);
+    hipLaunchKernelGGL(gemm_kgrp2_phased_kernel<true>, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0], a[1],
+                       (int32_t*)nullptr, pl, (float*)ws);
+    hipError_t err = launch_check(st);
+    if (err != hipSuccess || pl.chunks == 1) return err;
+    hipLaunchKernelGGL(tile_sum_kernel, dim3(TileP::BM / 4, (unsigned)(n - pl.whole)), dim3(256), 0, st, a[0], a[1], pl,
+                       (const float*)ws);
+    return launch_check(st);
 }
 
 // Experts ranked by row count, most first (ties to the lower index):

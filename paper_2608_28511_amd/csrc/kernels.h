@@ -41,10 +41,6 @@ hipError_t launch_seq_aux_loss(const float* logits, const int32_t* topk_idx, int
                                hipStream_t st);
 // sel_bias[e] += rate * sign(mean(counts) - counts[e])
 hipError_t launch_expert_bias_update(const int32_t* counts, int E, float rate, float* sel_bias, hipStream_t st);
-// out[m,n] = sum_c sum_{s=P-1..0} part[c][m][s*ldp+n] (fixed order; rows of part hold P*ldp)
-hipError_t launch_sum_planes(const float* part, int nchunk, int M, int N, int P, int ldp, float* out,
-                             hipStream_t st);
-int wgrad_chunks(int64_t rows, int M, int N);
 
 size_t route_ws_bytes(int64_t S, int E);
 // sigmoid: the production router (sigmoid scores, selection by score +
@@ -111,11 +107,11 @@ hipError_t launch_grouped_rows_mx(const uint8_t* Aq, const uint8_t* A_scale, con
                                   int64_t b_stride, void* C, int64_t ldc, int epi, moe_bf16* aux_out,
                                   const void* sched, int E, int64_t R, int N, int Kd, hipStream_t st);
 // KGRP mode: C_e[m, n] = sum over expert e's rows r of A[r, m] * B[r, n]  (fp32 out).
-// KGRP over a dense contraction cut into nchunk row ranges of kchunk rows:
-// C + c*c_stride = A[rows of chunk c]^T @ B[rows of chunk c]  (fp32 partials).
-hipError_t launch_chunked_wgrad(const moe_bf16* A, int64_t lda, const moe_bf16* B, int64_t ldb, float* C,
-                                int64_t ldc, int64_t c_stride, int nchunk, int64_t kchunk, int M, int N,
-                                int64_t R, hipStream_t st);
+// Dense weight gradients C_q [M_q, N_q] = A_q^T B_q over R rows (fp32 out, row-major and contiguous operands),
+// two at once or (M1 = N1 = 0) one; ws of dense_wgrad_ws_bytes holds the partial tiles.
+size_t dense_wgrad_ws_bytes(int64_t R, int M0, int N0, int M1, int N1);
+hipError_t launch_dense_wgrad2(const moe_bf16* A0, const moe_bf16* B0, float* C0, int M0, int N0, const moe_bf16* A1,
+                               const moe_bf16* B1, float* C1, int M1, int N1, int64_t R, void* ws, hipStream_t st);
 // Two KGRP products over the same expert segments in one launch (the expert
 // FFN's dW2 and dW1): the experts' items in `order` (required, from
 // launch_expert_order), the largest contractions first, dealt evenly to the

@@ -12,10 +12,8 @@
 //                         ds split into three bf16 planes hi / mid / lo
 //                         (sum within 2^-24 relative of ds, as for the forward
 //                         weight split) for the MFMA product below;
-//   dWr                   the grouped GEMM's k-grouped mode, x_r^T [hi|mid|lo]
-//                         over row chunks of S into fp32 partials, then
-//                         sum_planes_kernel adds planes (lo, mid, hi) and
-//                         chunks in a fixed order;
+//   dWr                   x_r^T [hi|mid|lo] as a dense weight gradient, then
+//                         sum_planes_kernel adds the planes (lo, mid, hi);
 //   colsum kernels        dbias: fixed-order column sums in two passes;
 //   router_dx_kernel      one wavefront per token: the K nonzero terms of
 //                         ds Wr^T in fp32 from a transposed copy of Wr.
@@ -293,46 +291,19 @@ __global__ __launch_bounds__(256) void router_dx_kernel(const float* __restrict_
     }
 }
 
-// out[m, n] = sum over chunks c (ascending) of sum over planes s = P-1 .. 0 of
-// part[c][m][s*ldp + n]; rows of part hold P*ldp values.
-__global__ __launch_bounds__(256) void sum_planes_kernel(const float* __restrict__ part, int nchunk, int M, int N,
-                                                         int P, int ldp, float* __restrict__ out) {
+// out[m, n] = sum over planes s = P-1 .. 0 of src[m][s*ldp + n].
+__global__ __launch_bounds__(256) void sum_planes_kernel(const float* __restrict__ src, int M, int N, int P, int ldp,
+                                                         float* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= (int64_t)M * N) return;
     const int64_t m = i / N, n = i - m * N;
-    const int64_t row = (int64_t)P * ldp, chunk = (int64_t)M * row;
     float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) {
-        float c_sum = 0.f;
-        for (int p = P - 1; p >= 0; --p) c_sum += part[c * chunk + m * row + (int64_t)p * ldp + n];
-        s += c_sum;
-    }
+    for (int p = P - 1; p >= 0; --p) s += src[(m * P + p) * ldp + n];
     out[i] = s;
 }
 
-hipError_t launch_sum_planes(const float* part, int nchunk, int M, int N, int P, int ldp, float* out,
-                             hipStream_t st) {
-    const int64_t n = (int64_t)M * N;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(sum_planes_kernel, dim3(grid_for(n, 256)), dim3(256), 0, st, part, nchunk, M, N, P, ldp,
-                       out);
-    return launch_check(st);
-}
-
-int wgrad_chunks(int64_t rows, int M, int N) {
-    // enough row chunks that the k-grouped GEMM has ~512 workgroups
-    const int64_t per = (int64_t)((M + 127) / 128) * ((N + 255) / 256);
-    int64_t n = (512 + per - 1) / per;
-    const int64_t max_n = (rows + 255) / 256;
-    if (n > max_n) n = max_n;
-    if (n < 1) n = 1;
-    if (n > 64) n = 64;
-    return (int)n;
-}
-
 struct RouterBwdWs {
-    float* ds; uint16_t* ds3; float* WrT; float* part; float* colpart; uint16_t* ds6; uint16_t* W6; size_t bytes;
-    int nchunk;
+    float* ds; uint16_t* ds3; float* WrT; float* dW3; void* part; float* colpart; uint16_t* ds6; uint16_t* W6; size_t bytes;
 };
 
 static int pad8(int e) { return (e + 7) / 8 * 8; }
@@ -344,11 +315,11 @@ static RouterBwdWs router_bwd_layout(char* base, int64_t S, int D, int E, bool d
     size_t off = 0;
     auto take = [&](size_t bytes) { void* p = base ? base + off : nullptr; off += (bytes + 255) / 256 * 256; return p; };
     const int Ep = pad8(E);
-    w.nchunk = wgrad_chunks(S, D, 3 * Ep);
     w.ds = (float*)take((size_t)S * E * 4);
     w.ds3 = (uint16_t*)take((size_t)S * 3 * Ep * 2);
     w.WrT = (float*)take((size_t)E * D * 4);
-    w.part = (float*)take((size_t)w.nchunk * D * 3 * Ep * 4);
+    w.dW3 = (float*)take((size_t)D * 3 * Ep * 4);
+    w.part = take(dense_wgrad_ws_bytes(S, D, 3 * Ep, 0, 0));
     w.colpart = (float*)take((size_t)colsum_chunks(S) * E * 4);
     if (dense) {
         w.ds6 = (uint16_t*)take((size_t)S * 6 * Ep * 2);
@@ -430,13 +401,12 @@ static hipError_t router_linear_bwd(const moe_bf16* x_r, const float* Wr, const 
                                     float* dWr, float* dbias, float* dx_r, hipStream_t st) {
     const int Ep = pad8(E);
     hipError_t err;
-    // dWr [D, E] = x_r^T [hi | mid | lo](ds), fp32 partials per row chunk
-    const int64_t kchunk = S > 0 ? (S + w.nchunk - 1) / w.nchunk : 1;
-    if ((err = launch_chunked_wgrad(x_r, D, (const moe_bf16*)w.ds3, 3 * (int64_t)Ep, w.part, 3 * (int64_t)Ep,
-                                    (int64_t)D * 3 * Ep, w.nchunk, kchunk, D, 3 * Ep, S, st)) != hipSuccess)
+    // dWr [D, E] = x_r^T [hi | mid | lo](ds), summed over the planes
+    if ((err = launch_dense_wgrad2(x_r, (const moe_bf16*)w.ds3, w.dW3, D, 3 * Ep, nullptr, nullptr, nullptr, 0, 0, S,
+                                   w.part, st)) != hipSuccess)
         return err;
-    // (an empty row range contributes zero partials: the k-grouped kernel writes its zero accumulators)
-    if ((err = launch_sum_planes(w.part, w.nchunk, D, E, 3, Ep, dWr, st)) != hipSuccess) return err;
+    hipLaunchKernelGGL(sum_planes_kernel, dim3(grid_for((int64_t)D * E, 256)), dim3(256), 0, st, w.dW3, D, E, 3, Ep, dWr);
+    if ((err = launch_check(st)) != hipSuccess) return err;
     if (dbias != nullptr) {
         const int nch = colsum_chunks(S);
         const int64_t chunk_rows = (S + nch - 1) / nch;

@@ -132,6 +132,42 @@ def test_weight_gradients(D, F, heavy):
             assert torch.equal(dW2[e], h[a:b].float().T @ dy[a:b].float()), e
 
 
+@pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 1000, 5000])
+@pytest.mark.parametrize("M,N", [(8, 8), (264, 248), (1024, 776)])
+def test_dense_weight_gradient(R, M, N):
+    """Pieces of the contraction and their sum: none to 64 of them, the last ones short."""
+    g = torch.Generator(device=DEV).manual_seed(R + M)
+    x, dout, W = _ints(g, (R, M), 1), _ints(g, (R, N), 1), _ints(g, (M, N), 1)
+    _, dW = layer.latent_proj_bwd(x, W, dout, want_dx=False)
+    assert torch.equal(dW, x.float().T @ dout.float())
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_dense_weight_gradient_whole_tiles(shift):
+    """More tiles than a device's round: whole ones, then pieces; dW aligned to 16 and to 4 bytes."""
+    R, M, N = 520, 4112, 4104
+    g = torch.Generator(device=DEV).manual_seed(3)
+    x, dout, W = _ints(g, (R, M), 1), _ints(g, (R, N), 1), _ints(g, (M, N), 1)
+    ws = torch.empty(L.moe_latent_proj_bwd_workspace_bytes(R, M, N), dtype=torch.uint8, device=DEV)
+    buf = torch.full((M * N + 8,), 7.0, device=DEV)
+    dW = buf[shift:shift + M * N].view(M, N)
+    L.moe_latent_proj_bwd(x, W, dout, R, M, N, None, dW, ws)
+    assert torch.equal(dW, x.float().T @ dout.float())
+    assert (buf[:shift] == 7).all() and (buf[shift + M * N:] == 7).all()
+
+
+@pytest.mark.parametrize("S,D,F", [(700, 264, 520), (3000, 2056, 4360)])
+def test_dense_weight_gradient_pair(S, D, F):
+    """The shared expert's two gradients in one launch, their tiles in one list."""
+    g = torch.Generator(device=DEV).manual_seed(S)
+    x, h, u = _ints(g, (S, D), 1), _ints(g, (S, F), 1), _ints(g, (S, F), 2)
+    dy = _ints(g, (S, D), 1) * (torch.rand((S, D), generator=g, device=DEV) < 0.02)
+    W1, W2 = _ints(g, (D, F), 1), _ints(g, (F, D), 1)
+    _, dW1, dW2 = layer.shared_expert_bwd(x, u, h, dy, W1, W2, want_dx=False)
+    du = ((dy.float() @ W2.float().T) * 2 * u.float().clamp(min=0)).to(torch.bfloat16)
+    assert torch.equal(dW1, x.float().T @ du.float()) and torch.equal(dW2, h.float().T @ dy.float())
+
+
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fp32_outputs(accumulate):
     """The shared expert's fp32 products, forward and (with an addend) backward."""
