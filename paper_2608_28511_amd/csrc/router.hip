@@ -10,7 +10,8 @@
 // the bfloat16 artificial intelligence datatype for higher-precision
 // computations", ARITH 2019).
 //
-// Two launches:
+// One launch for the calls that it fits into one round of workgroups
+// (router_small_kernel), else two:
 //   router_split_kernel   Wr [D, E] fp32 -> three bf16 planes [3][E][D]
 //                         (transposed: each plane is K-contiguous like x);
 //   router_logits_kernel  TM tokens x RE experts per workgroup (128 x 64 on
@@ -37,6 +38,17 @@
 namespace moe {
 
 
+// Two weights' three bf16 terms, packed (the first in the low half).
+__device__ __forceinline__ void split_pair(float w0, float w1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    const uint32_t h0 = f32_to_bf16(w0), h1 = f32_to_bf16(w1);
+    const float a0 = w0 - __uint_as_float(h0 << 16), a1 = w1 - __uint_as_float(h1 << 16);
+    const uint32_t m0 = f32_to_bf16(a0), m1 = f32_to_bf16(a1);
+    const uint32_t l0 = f32_to_bf16(a0 - __uint_as_float(m0 << 16)), l1 = f32_to_bf16(a1 - __uint_as_float(m1 << 16));
+    hi = h0 | (h1 << 16);
+    mid = m0 | (m1 << 16);
+    lo = l0 | (l1 << 16);
+}
+
 // ---- split: one lane per (expert, 8-wide d chunk) -------------------------
 // A wave takes 8 experts x 64 d: lane l handles expert 8 * wave-slot + l / 8
 // and d chunk l % 8, so the eight lanes of an expert store its 64 d of each
@@ -55,19 +67,7 @@ __global__ __launch_bounds__(256) void router_split_kernel(const float* __restri
     uint32_t hb[4], mb[4], lb[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        uint32_t p[3][2];
-#pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const float x = w[2 * u + v];
-            const uint32_t hi = f32_to_bf16(x);
-            const float r1 = x - __uint_as_float(hi << 16);
-            const uint32_t mid = f32_to_bf16(r1);
-            const uint32_t lo = f32_to_bf16(r1 - __uint_as_float(mid << 16));
-            p[0][v] = hi; p[1][v] = mid; p[2][v] = lo;
-        }
-        hb[u] = p[0][0] | (p[0][1] << 16);
-        mb[u] = p[1][0] | (p[1][1] << 16);
-        lb[u] = p[2][0] | (p[2][1] << 16);
+        split_pair(w[2 * u], w[2 * u + 1], hb[u], mb[u], lb[u]);
     }
     const int64_t plane = (int64_t)E * D;
     uint16_t* dst = w3 + (int64_t)e * D + d;
@@ -202,15 +202,111 @@ __global__ __launch_bounds__(TM / WM * (RE / WN) * 64, 1) void router_logits_ker
     }
 }
 
+// ---- few tokens: split and product in one launch ---------------------------
+// 16 MI tokens x 16 experts per workgroup, its eight waves sharing out the
+// 32-wide d steps.  A lane loads its fragments straight from memory (16 bytes
+// of x; eight rows of the fp32 weight, 16 consecutive experts a row) and
+// splits the weights in registers, so there is no split launch, no LDS ring to
+// fill and no chain over all of D: latency is what bounds a small call.  The
+// waves' partial sums are added in wave order.
+template <int MI, int U>   // U: d steps of a wave loaded together
+__global__ __launch_bounds__(512) void router_small_kernel(const uint16_t* __restrict__ x, const float* __restrict__ Wr,
+                                                           const float* __restrict__ bias, int64_t S, int D, int E,
+                                                           float* __restrict__ logits) {
+    constexpr int kWv = 8;
+    __shared__ f32x4 red[kWv][MI][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t t0 = (int64_t)blockIdx.x * (16 * MI);
+    const int e0 = blockIdx.y * 16;
+    const int r = lane & 15, kq = (lane >> 4) * 8;
+    const bool e_ok = e0 + r < E;
+    f32x4 acc[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nks = (D + 31) / 32;
+    for (int ks = wave; ks < nks; ks += kWv * U) {
+        float w[U][8];
+        uint4 xv[U][MI];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = (ks + u * kWv) * 32 + kq;   // D is a multiple of 8: the lane's 8 d are whole
+            const bool k_ok = k < D;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) w[u][q] = k_ok && e_ok ? Wr[(int64_t)(k + q) * E + e0 + r] : 0.f;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int64_t t = t0 + i * 16 + r;
+                xv[u][i] = k_ok && t < S ? *(const uint4*)(x + t * D + k) : make_uint4(0, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint32_t pl[3][4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) split_pair(w[u][2 * v], w[u][2 * v + 1], pl[0][v], pl[1][v], pl[2][v]);
+#pragma unroll
+            for (int s = 2; s >= 0; --s) {   // lo, mid, hi: smaller terms first
+                const u32x4 wv = {pl[s][0], pl[s][1], pl[s][2], pl[s][3]};
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv),
+                                                                     __builtin_bit_cast(bf16x8, xv[u][i]), acc[i], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) red[wave][i][lane] = acc[i];
+    __syncthreads();
+    if (wave >= MI) return;
+    f32x4 v = red[0][wave][lane];
+#pragma unroll
+    for (int q = 1; q < kWv; ++q) {
+        const f32x4 o = red[q][wave][lane];
+        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+    }
+    const int64_t t = t0 + wave * 16 + r;
+    const int e = e0 + 4 * (lane >> 4);
+    if (t >= S) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (e + q < E) logits[t * E + e + q] = v[q] + (bias != nullptr ? bias[e + q] : 0.f);
+}
+
+template <int MI>
+static void launch_router_small(const moe_bf16* x, const float* Wr, const float* bias, int64_t S, int D, int E,
+                                float* logits, dim3 g, hipStream_t st) {
+    if (D <= 8 * 32)   // one step a wave
+        hipLaunchKernelGGL((router_small_kernel<MI, 1>), g, dim3(512), 0, st, x, Wr, bias, S, D, E, logits);
+    else
+        hipLaunchKernelGGL((router_small_kernel<MI, MI == 4 ? 2 : 4>), g, dim3(512), 0, st, x, Wr, bias, S, D, E, logits);
+}
+
 size_t router_ws_bytes(int D, int E) { return ((size_t)3 * E * D * 2 + 255) / 256 * 256; }
 
 hipError_t launch_router_logits(const moe_bf16* x, const float* Wr, const float* bias, int64_t S,
                                 int D, int E, float* logits, void* ws, hipStream_t st) {
+    if (S == 0) return hipSuccess;
+    // One launch while its workgroups fit the device at once, in the fewest
+    // tokens each that do (measured against split + tiles, their launch gap not
+    // counted, us): 64 tokens x 64 experts x D 2,048 6.8 / 13.8; 1,024 x 64 7.6 /
+    // 14.2; 2,048 x 64 (32 tokens a workgroup) 9.2 / 14.5; 4,096 x 64 (64) 12.8 / 16.9;
+    // 512 x 512 x 2,688 (64) 17.6 / 22.0; 512 x 8 x 256 3.4 / 6.0.  Past one round
+    // every workgroup's reading and splitting of the weights repeats: 8,192 x 64 x
+    // 2,048 22.0 / 17.1.
+    for (int mi = 1; mi <= 4; mi *= 2) {
+        const int64_t mt = (S + 16 * mi - 1) / (16 * mi), nt = (E + 15) / 16;
+        if (mt * nt > cu_count()) continue;
+        const dim3 g((unsigned)mt, (unsigned)nt);
+        if (mi == 1) launch_router_small<1>(x, Wr, bias, S, D, E, logits, g, st);
+        else if (mi == 2) launch_router_small<2>(x, Wr, bias, S, D, E, logits, g, st);
+        else launch_router_small<4>(x, Wr, bias, S, D, E, logits, g, st);
+        return launch_check(st);
+    }
     uint16_t* w3 = (uint16_t*)ws;
     hipLaunchKernelGGL(router_split_kernel, dim3((unsigned)((D + 63) / 64), (unsigned)((E + 31) / 32)),
                        dim3(256), 0, st, Wr, D, E, w3);
     hipError_t err = launch_check(st);
-    if (err != hipSuccess || S == 0) return err;
+    if (err != hipSuccess) return err;
     // 16-byte output stores only where every row start is 16-byte aligned
     const bool vec_out = (E % 4) == 0 && ((uintptr_t)logits % 16) == 0;
     // The tile whose rounds of workgroups over the compute units cost the
