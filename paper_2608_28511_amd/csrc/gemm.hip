@@ -11,7 +11,7 @@
 //   KGRP mode   C_e[m, n] = sum_{r in segment e} A[r, m] * B[r, n]  (wgrad:
 //               the contraction runs over the expert's ragged rows).
 //
-// Three block tiles on 512 threads, 8 wavefronts in a 2 x 4 grid
+// Four block tiles on 512 threads, 8 wavefronts, in a 2 x 4 grid but for one
 // (v_mfma_f32_16x16x32_bf16):
 //   phased 256 x 256 (phased.h), 64 k per k tile: the dense weight gradients, and
 //     ROWS launches and the experts' weight gradients where its coarser tile
@@ -21,9 +21,11 @@
 //     under it the chip is power bound: 1.6-1.75 GHz at 1.2-1.36 PFLOP/s.
 //   128 x 256, 64 k per stage, 3-stage ring of 48 KB stages: the other ROWS
 //     launches and the shortest weight gradients;
+//   128 x 128, 4-stage ring of 32 KB stages, waves of 32 x 64 in a 4 x 2 grid:
+//     the smallest ROWS launches (rows_kind);
 //   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: the products over
 //     an MX-FP8 A that are long enough.
-// For the last two neither the MFMAs nor copy bandwidth bound the kernel: all
+// For all but the first neither the MFMAs nor copy bandwidth bound the kernel: all
 // eight waves read after each barrier and then all multiply, and the waits
 // are on LDS and copy latency.
 // One workgroup fills a CU's LDS, so each SIMD runs two wavefronts: one wave's
@@ -98,11 +100,13 @@ constexpr int kGroupM = 8;
 // Block tile BM x BN with KD contraction elements per ring stage and a ring
 // of STAGES stages.  AMX: A is MX-FP8 (codes, one byte per element, and the
 // stage's block scales; see MxDma) instead of bf16.
-template <int BM_, int KD_, int STAGES_, bool AMX_ = false>
+template <int BM_, int KD_, int STAGES_, bool AMX_ = false, int BN_ = 256>
 struct Tile {
-    static constexpr int BM = BM_, KD = KD_, kStages = STAGES_;
+    static constexpr int BM = BM_, BN = BN_, KD = KD_, kStages = STAGES_;
     static constexpr bool kAmx = AMX_;
-    static constexpr int MI = BM / 32;          // A fragments (16 rows) per wave: waves cover BM/2 rows
+    static constexpr int kWaveN = BN / 64;      // waves side by side, 64 columns each
+    static constexpr int kWaveRows = BM / (kWaves / kWaveN);
+    static constexpr int MI = kWaveRows / 16;   // A fragments (16 rows) per wave
     static constexpr int kKK = KD / 32;         // MFMA k steps per stage
     static constexpr int kCodeBytes = BM * KD;  // AMX: the stage's codes, then its scale words
     static constexpr int kSclBytes = AMX_ ? kWaves * 64 * 4 : 0;
@@ -115,9 +119,11 @@ struct Tile {
 };
 using TileS = Tile<128, 64, 3>;   // 144 KB ring (+16 KB epilogue staging)
 using TileL = Tile<256, 32, 4>;   // 128 KB ring
+using TileN = Tile<128, 64, 4, false, 128>;   // 128 KB ring; waves of 32 rows
 using TileSX = Tile<128, 64, 3, true>;   // MX-FP8 A: 126 KB ring
 using TileLX = Tile<256, 32, 4, true>;   // 104 KB ring
-static_assert(TileS::kRingBytes + kEpiBytes <= 160 * 1024 && TileL::kRingBytes + kEpiBytes <= 160 * 1024 &&
+static_assert(TileN::kRingBytes + kEpiBytes <= 160 * 1024 &&
+                  TileS::kRingBytes + kEpiBytes <= 160 * 1024 && TileL::kRingBytes + kEpiBytes <= 160 * 1024 &&
                   TileSX::kRingBytes + kEpiBytes <= 160 * 1024 && TileLX::kRingBytes + kEpiBytes <= 160 * 1024,
               "LDS budget");
 
@@ -262,7 +268,7 @@ __device__ __forceinline__ void mma_stage(f32x4 (&acc)[T::MI][4], const uint32_t
         for (int j = 0; j < 4; ++j) {
             constexpr uint32_t so = (S & 1) * T::kBBytes;
             if constexpr (B_K) bfg[j] = lds_b128(bbase[S >> 1][kk] + so + j * T::kFrag);
-            else bfg[j] = lds_tr_pair(bbase[S >> 1][j] + so + kk * 64 * BN, 8 * BN);
+            else bfg[j] = lds_tr_pair(bbase[S >> 1][j] + so + kk * 64 * T::BN, 8 * T::BN);
         }
         if (next) {
             if (T::kKK == 1) {
@@ -289,12 +295,12 @@ __device__ __forceinline__ void frag_bases(uint32_t (&abase)[NA], uint32_t (&bba
                                            uint32_t ldsB, int wm, int wn, int lane) {
 #pragma unroll
     for (int i = 0; i < NA; ++i)
-        abase[i] = ldsA + (T::kAmx ? mx_row_base<T::KD>(wm * (T::BM / 2), i, lane)
-                           : A_K  ? row_base<T::KD>(wm * (T::BM / 2), i, lane)
-                                  : col_base<T::BM>(wm * (T::BM / 2) + i * 16, lane));
+        abase[i] = ldsA + (T::kAmx ? mx_row_base<T::KD>(wm * T::kWaveRows, i, lane)
+                           : A_K  ? row_base<T::KD>(wm * T::kWaveRows, i, lane)
+                                  : col_base<T::BM>(wm * T::kWaveRows + i * 16, lane));
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        const uint32_t o = B_K ? row_base<T::KD>(wn * 64, j, lane) : col_base<BN>(wn * 64 + j * 16, lane);
+        const uint32_t o = B_K ? row_base<T::KD>(wn * 64, j, lane) : col_base<T::BN>(wn * 64 + j * 16, lane);
         bbase[0][j] = ldsB + o;                    // stages 0 and 1
         bbase[1][j] = ldsB + 2 * T::kBBytes + o;   // stages 2 and 3 (immediate offsets reach 64 KB)
     }
@@ -533,8 +539,8 @@ struct RowsTile {
 
 static_assert(kSchedGroupM == kGroupM, "schedule runs and dense groups take the same m-tiles");
 
-template <int BM>
-__device__ __forceinline__ RowsTile rows_tile(const GemmArgs& p, const int4* tiles, int m_count, int w,
+template <int BM, int BN>
+__device__ __forceinline__ RowsTile rows_tile(const GemmArgs& p, const int4* tiles, int m_count, int n_tiles, int w,
                                               int m_base) {
     typedef const __attribute__((address_space(4))) int32_t* cptr;
     // item w of the m-tiles [m_base, m_base + m_count) x all n-tiles, taken a
@@ -547,19 +553,19 @@ __device__ __forceinline__ RowsTile rows_tile(const GemmArgs& p, const int4* til
         // run of s m-tiles covers s * n_tiles consecutive items); the table
         // is written by an earlier launch and read-only here: scalar loads
         // through the constant address space
-        const int q = m_base + w / p.n_tiles;
+        const int q = m_base + w / n_tiles;
         const int packed = ((cptr)(tiles + q))[3];
         int a = packed >> 4, b = a + (packed & 15);
         a = a > m_base ? a : m_base;
         b = b < m_base + m_count ? b : m_base + m_count;
         if (a > q || b <= q) { a = q; b = q + 1; }   // an entry that does not hold q: take q alone
         const int s = b - a;
-        const int in = w - (a - m_base) * p.n_tiles;
+        const int in = w - (a - m_base) * n_tiles;
         mt = a + in % s;
         nt = in / s;
-        nt = nt < p.n_tiles ? nt : p.n_tiles - 1;
+        nt = nt < n_tiles ? nt : n_tiles - 1;
     } else {
-        const int width = kGroupM * p.n_tiles;
+        const int width = kGroupM * n_tiles;
         const int group = w / width;
         const int first_m = group * kGroupM;
         const int gsz = (m_count - first_m) < kGroupM ? (m_count - first_m) : kGroupM;
@@ -712,11 +718,11 @@ __device__ __forceinline__ void f32_store(const f32x4 (&acc)[MI][4], float* C, i
 // not a multiple of 64.
 template <class T, bool B_K, int EPI, bool KTAIL>
 __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const int4* tiles, int m_total) {
-    constexpr int BM = T::BM, MI = T::MI, KD = T::KD, kStages = T::kStages;
+    constexpr int BM = T::BM, BN = T::BN, MI = T::MI, KD = T::KD, kStages = T::kStages;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 2, wn = wave & 3;
+    const int wm = wave / T::kWaveN, wn = wave % T::kWaveN;
 
     // Each XCD's G / 8 workgroups (workgroups go to XCDs round-robin) take a
     // contiguous eighth of the m-tiles, all n-tiles, in group-M order; this
@@ -729,7 +735,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
     const int xcd = (int)(blockIdx.x % kXcds), lx = (int)(blockIdx.x / kXcds);
     const int m_base = (int)((int64_t)m_total * xcd / kXcds);
     const int m_count = (int)((int64_t)m_total * (xcd + 1) / kXcds) - m_base;
-    const int n_work = m_count * p.n_tiles;
+    const int n_tiles = BN == 256 ? p.n_tiles : (p.N + BN - 1) / BN;
+    const int n_work = m_count * n_tiles;
     const int n_mine = lx < n_work ? (n_work - lx + Gx - 1) / Gx : 0;
     const int nk = (p.Kd + KD - 1) / KD;
     const int g_total = n_mine * nk;  // (tile, k step) pairs
@@ -745,7 +752,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
     constexpr int kSA = DA::kSlots, kSB = DmaTile<B_K, BN, KD>::kSlots;
     constexpr int kPerStage = kSA + kSB;
     auto dma_tile = [&](int j) {
-        const RowsTile t = rows_tile<BM>(p, tiles, m_count, lx + j * Gx, m_base);
+        const RowsTile t = rows_tile<BM, BN>(p, tiles, m_count, n_tiles, lx + j * Gx, m_base);
         if constexpr (T::kAmx)
             da.init((const uint8_t*)p.A, p.A_scale, p.scale_bytes, t.row0, t.row_hi, p.Kd, wave, lane);
         else if (p.a_perm != nullptr)
@@ -765,7 +772,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
     // AMX: the lane's rows are r0 + 16 i; their scale windows sit 4 * kLPR
     // bytes apart, and all share the in-window byte offset (row * nb + kb) & 3.
     const int nb = p.Kd / 32;
-    const int r0_lane = wm * (BM / 2) + (lane & 15);
+    const int r0_lane = wm * T::kWaveRows + (lane & 15);
     uint32_t sbase = 0, rnb = 0;
     if constexpr (T::kAmx) {
         sbase = ldsA + T::kCodeBytes + (uint32_t)r0_lane * 4u * MxDma<T>::kLPR;
@@ -784,7 +791,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
 
     int kc = 0;   // k step of the tile being computed
     int jc = 0;   // its index in this workgroup's list
-    RowsTile cur = rows_tile<BM>(p, tiles, m_count, lx, m_base);
+    RowsTile cur = rows_tile<BM, BN>(p, tiles, m_count, n_tiles, lx, m_base);
     u32x2 uu[MI][4];   // dgrad: the tile's pre-activations
 
     auto step = [&](auto stage_c, int g) {
@@ -797,8 +804,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
         stage_barrier();
         if constexpr (EPI == EPI_DRELU2)
             if (kc == 0)
-                drelu2_load(uu, p.aux_in, p.ldc, p.N, cur.row0 + wm * (BM / 2),
-                            cur.row_hi - (cur.row0 + wm * (BM / 2)), cur.n0 + wn * 64, lane);
+                drelu2_load(uu, p.aux_in, p.ldc, p.N, cur.row0 + wm * T::kWaveRows,
+                            cur.row_hi - (cur.row0 + wm * T::kWaveRows), cur.n0 + wn * 64, lane);
         const bool next = g + kStages - 1 < g_total;
         if (next && kd == 0) dma_tile(jd);
         uint32_t sb = 0;
@@ -807,7 +814,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
                                           sb);
         if (++kd == nk) { kd = 0; ++jd; }
         if (kc == nk - 1) {
-            const int rbase = cur.row0 + wm * (BM / 2);
+            const int rbase = cur.row0 + wm * T::kWaveRows;
             const int nrows = cur.row_hi - rbase;
             const int cbase = cur.n0 + wn * 64;
             if constexpr (EPI == EPI_DRELU2) {
@@ -823,7 +830,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& p, char* smem, const i
             zero_acc(acc);
             kc = 0;
             ++jc;
-            if (jc < n_mine) cur = rows_tile<BM>(p, tiles, m_count, lx + jc * Gx, m_base);
+            if (jc < n_mine) cur = rows_tile<BM, BN>(p, tiles, m_count, n_tiles, lx + jc * Gx, m_base);
         } else {
             ++kc;
         }
@@ -1328,23 +1335,25 @@ __device__ __forceinline__ bool take_tall_tiles(int m_small, int m_tall, int n_t
 constexpr int kRowsSmemBytes = 160 * 1024;
 static_assert(TileS::kRingBytes + kEpiBytes <= kRowsSmemBytes && kListOff < kRowsSmemBytes, "LDS budget");
 
-// The ROWS launch.  MAYBE: the launch may take the phased tile, which the
-// kernel decides from the tile schedule's counts (known only after routing);
-// without it the kernel holds the 128-row body alone (see maybe_phased).
-template <bool B_K, int EPI, bool KTAIL, bool MAYBE>
+// The ROWS launch.  kMaybePhased: the launch may take the phased tile, which
+// the kernel decides from the tile schedule's counts (known only after
+// routing); otherwise the kernel holds one 128-row body alone, 256 or (kNarrow)
+// 128 columns wide (see rows_kind).
+enum RowsKind { kWide, kNarrow, kMaybePhased };
+template <bool B_K, int EPI, bool KTAIL, RowsKind KIND>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_rows_kernel(GemmArgs p) {
     __shared__ __attribute__((aligned(1024))) char smem[kRowsSmemBytes];
     typedef const __attribute__((address_space(4))) int32_t* cnt_ptr;
     // the table's count, never beyond the table (the builder caps it too)
     const int m_small = p.mtile_total != nullptr ? min(*(cnt_ptr)p.mtile_total, p.m_tiles) : p.m_tiles;
-    if constexpr (MAYBE) {
+    if constexpr (KIND == kMaybePhased) {
         const int m_tall = p.mtile_total_l != nullptr ? min(*(cnt_ptr)p.mtile_total_l, p.m_tiles_l) : p.m_tiles_l;
         if (take_phased(m_small, m_tall, p.n_tiles, (int)gridDim.x)) {
             rows_body_phased<B_K, EPI, KTAIL>(p, smem, p.tiles_l, m_tall);
             return;
         }
     }
-    rows_body<TileS, B_K, EPI, KTAIL>(p, smem, p.tiles, m_small);
+    rows_body<std::conditional_t<KIND == kNarrow, TileN, TileS>, B_K, EPI, KTAIL>(p, smem, p.tiles, m_small);
 }
 
 constexpr int kRowsMxSmemBytes =
@@ -1411,35 +1420,60 @@ static int64_t rows_grid(const GemmArgs& a) {
     return need < G ? need : G;
 }
 
-// Whether a ROWS launch can take the phased tile.  Dense rows: the rule itself.
+// Workgroups that take the 128-column tiles of every XCD's m-tiles in one
+// round.  Expert segments: m-tiles sum to ceil(c / 128) <= 1 + (c - 1) / 128 over
+// the experts with rows, at most min(R, E) of them.
+static int64_t narrow_grid(const GemmArgs& a) {
+    const int64_t used = std::min<int64_t>(a.R, a.E);
+    const int64_t m = a.tiles != nullptr ? std::min<int64_t>(a.m_tiles, used + (a.R - used) / TileN::BM) : a.m_tiles;
+    return (m + kXcds - 1) / kXcds * ((a.N + TileN::BN - 1) / TileN::BN) * kXcds;
+}
+
+// The body of a ROWS launch, G workgroups of the full width.
+// Narrow: the tiles of half the width take a single round.  Such a launch is one
+// chain of k tiles a workgroup, bound by the latency of each; half the tile
+// takes 0.65-0.75 of the wide one's time (us, wide / narrow: 8 experts x 128 rows,
+// 256 -> 512 8.3 / 6.8 and back 11.9 / 8.4; 8 x 32, 2,048 -> 1,024 29.2 / 20.5; 8 x 8,
+// 2,688 -> 3,520 37.9 / 27.7; dense 1,024 x 2,688 x 2,688 37.6 / 27.5; dense 32 x 2,688 x
+// 672, whose few wide tiles share one XCD, 98 / 24).  At narrow rounds 2 against
+// wide rounds 1 it takes 0.98-1.25, at 3 : 2 0.97, at 4 : 2 1.04-1.21; 2 : 2 takes 0.65, but
+// the counts behind it are a bound and routing may leave the wide tile one round.
+// Phased, dense rows: the rule itself.
 // Expert segments, whose counts the host does not know: not with a single
 // round of 128-row tiles, and not below 80 rows per expert, where routing
 // without strong skew leaves no expert over 128 rows and both heights the same
 // tiles.  Such launches are short, and the kernel with both bodies costs them
 // up to 1 us (18.0 against 17.6 us at 1,024 rows of 8 experts, 43.8 against 43.0
 // us at 1,024 rows of 64).  The phased body needs two k tiles.
-static bool maybe_phased(const GemmArgs& a, int64_t G) {
-    if (a.Kd <= TileP::KD) return false;
-    if (a.tiles == nullptr) return take_phased(a.m_tiles, a.m_tiles_l, a.n_tiles, (int)G);
-    return tile_rounds(a.m_tiles, a.n_tiles, (int)G) > 1 && a.R >= 80 * (int64_t)a.E;
+static RowsKind rows_kind(const GemmArgs& a, int64_t G) {
+    if (narrow_grid(a) <= persistent_grid()) return kNarrow;
+    if (a.Kd <= TileP::KD) return kWide;
+    const bool phased = a.tiles == nullptr
+                            ? take_phased(a.m_tiles, a.m_tiles_l, a.n_tiles, (int)G)
+                            : tile_rounds(a.m_tiles, a.n_tiles, (int)G) > 1 && a.R >= 80 * (int64_t)a.E;
+    return phased ? kMaybePhased : kWide;
 }
 
 template <bool B_K, int EPI, bool KTAIL>
-static void launch_rows_kernel(const GemmArgs& a, int64_t G, hipStream_t st) {
-    if (maybe_phased(a, G))
-        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, true>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+static void launch_rows_kernel(const GemmArgs& a, hipStream_t st) {
+    const int64_t wide = rows_grid(a);
+    const RowsKind kind = rows_kind(a, wide);
+    const dim3 G((unsigned)(kind == kNarrow ? narrow_grid(a) : wide)), B(kGemmThreads);
+    if (kind == kNarrow)
+        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, kNarrow>), G, B, 0, st, a);
+    else if (kind == kWide)
+        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, kWide>), G, B, 0, st, a);
     else
-        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, false>), dim3((unsigned)G), dim3(kGemmThreads), 0, st, a);
+        hipLaunchKernelGGL((gemm_rows_kernel<B_K, EPI, KTAIL, kMaybePhased>), G, B, 0, st, a);
 }
 
 template <bool B_K, int EPI>
 static hipError_t launch_rows(const GemmArgs& a, hipStream_t st) {
-    const int64_t G = rows_grid(a);
-    if (G == 0) return hipSuccess;
+    if (rows_grid(a) == 0) return hipSuccess;
     if (a.Kd % TileS::KD != 0)
-        launch_rows_kernel<B_K, EPI, true>(a, G, st);
+        launch_rows_kernel<B_K, EPI, true>(a, st);
     else
-        launch_rows_kernel<B_K, EPI, false>(a, G, st);
+        launch_rows_kernel<B_K, EPI, false>(a, st);
     return launch_check(st);
 }
 
