@@ -203,82 +203,128 @@ __global__ __launch_bounds__(TM / WM * (RE / WN) * 64, 1) void router_logits_ker
 }
 
 // ---- few tokens: split and product in one launch ---------------------------
-// 16 MI tokens x 16 experts per workgroup, its eight waves sharing out the
-// 32-wide d steps.  A lane loads its fragments straight from memory (16 bytes
-// of x; eight rows of the fp32 weight, 16 consecutive experts a row) and
-// splits the weights in registers, so there is no split launch, no LDS ring to
-// fill and no chain over all of D: latency is what bounds a small call.  The
-// waves' partial sums are added in wave order.
-template <int MI, int U>   // U: d steps of a wave loaded together
-__global__ __launch_bounds__(512) void router_small_kernel(const uint16_t* __restrict__ x, const float* __restrict__ Wr,
-                                                           const float* __restrict__ bias, int64_t S, int D, int E,
-                                                           float* __restrict__ logits) {
-    constexpr int kWv = 8;
-    __shared__ f32x4 red[kWv][MI][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t t0 = (int64_t)blockIdx.x * (16 * MI);
+// 16 MI tokens x 16 experts per workgroup, D in stages of four 32-wide steps.
+// Four waves, a step of each stage apiece, load the fp32 weights AHEAD stages
+// ahead (a lane eight rows, 16 consecutive experts a row), split them in registers
+// and leave the planes' fragments in LDS; MI waves, one per 16 tokens, read them
+// while they run the products of the stage before, x fragments straight from
+// memory.  There is no split launch and no copy ring to fill: latency is what
+// bounds a small call.  A logit is the same chain of products as in
+// router_logits_kernel (32-wide d steps in order; lo, mid, hi), so a token's
+// logits do not depend, to the last bit, on how many tokens share its call.
+// That chain (192 dependent MFMAs at D = 2,048) is paid for: with D shared out to
+// eight waves and their sums added, 64 tokens x 64 experts took 6.8 us, not 8.2,
+// but their last bits then changed with the size of the call.
+constexpr uint32_t kDropOffset = 0x80000000u;   // beyond any descriptor's range: reads as zero
+constexpr int kSmallSteps = 4;                  // d steps per stage, and waves that split
+
+template <int MI, int AHEAD>
+__global__ __launch_bounds__((kSmallSteps + MI) * 64) void router_small_kernel(
+    const uint16_t* __restrict__ x, const float* __restrict__ Wr, const float* __restrict__ bias, int64_t S, int D,
+    int E, float* __restrict__ logits) {
+    __shared__ u32x4 planes[2][kSmallSteps][3][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int e0 = blockIdx.y * 16;
     const int r = lane & 15, kq = (lane >> 4) * 8;
-    const bool e_ok = e0 + r < E;
-    f32x4 acc[MI];
+    const int nst = (D + 32 * kSmallSteps - 1) / (32 * kSmallSteps);
+    // Every wave passes one barrier per stage, when the stage's planes are written.
+    // They are read before the next barrier, after which the stage two later
+    // takes their place.
+    auto stage_written = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    if (wave >= MI) {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((void*)Wr, 0, (int32_t)((uint32_t)D * (uint32_t)E * 4), 0x00020000);
+        const uint32_t ld = (uint32_t)E * 4;
+        float w[AHEAD][8];
+        auto load = [&](float (&v)[8], int st) {
+            const uint32_t k = (uint32_t)(st * kSmallSteps + wave - MI) * 32 + kq;   // D % 8 == 0: the lane's 8 d are whole
+            const uint32_t o = e0 + r < E ? k * ld + (uint32_t)(e0 + r) * 4 : kDropOffset;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nks = (D + 31) / 32;
-    for (int ks = wave; ks < nks; ks += kWv * U) {
-        float w[U][8];
-        uint4 xv[U][MI];
+            for (int q = 0; q < 8; ++q)
+                v[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o + (uint32_t)q * ld, 0, 0));
+        };
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = (ks + u * kWv) * 32 + kq;   // D is a multiple of 8: the lane's 8 d are whole
-            const bool k_ok = k < D;
+        for (int a = 0; a < AHEAD; ++a) load(w[a], a);
+        for (int st0 = 0; st0 < nst; st0 += AHEAD) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) w[u][q] = k_ok && e_ok ? Wr[(int64_t)(k + q) * E + e0 + r] : 0.f;
+            for (int a = 0; a < AHEAD; ++a) {
+                const int st = st0 + a;
+                if (st >= nst) break;
+                uint32_t pl[3][4];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                const int64_t t = t0 + i * 16 + r;
-                xv[u][i] = k_ok && t < S ? *(const uint4*)(x + t * D + k) : make_uint4(0, 0, 0, 0);
+                for (int v = 0; v < 4; ++v) split_pair(w[a][2 * v], w[a][2 * v + 1], pl[0][v], pl[1][v], pl[2][v]);
+#pragma unroll
+                for (int s = 0; s < 3; ++s)
+                    planes[st & 1][wave - MI][s][lane] = u32x4{pl[s][0], pl[s][1], pl[s][2], pl[s][3]};
+                if (st + AHEAD < nst) load(w[a], st + AHEAD);
+                stage_written();
             }
         }
+        return;
+    }
+
+    const int64_t t0 = ((int64_t)blockIdx.x * MI + wave) * 16, t = t0 + r;
+    const int64_t rows = S - t0 < 16 ? S - t0 : 16;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(x + t0 * D), 0, rows > 0 ? (int32_t)(rows * D * 2) : 0, 0x00020000);
+    u32x4 xv[AHEAD][kSmallSteps];
+    auto load_x = [&](u32x4 (&v)[kSmallSteps], int st) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint32_t pl[3][4];
+        for (int u = 0; u < kSmallSteps; ++u) {
+            const int k = (st * kSmallSteps + u) * 32 + kq;
+            v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, k < D ? (uint32_t)(r * D + k) * 2 : kDropOffset, 0, 0);
+        }
+    };
+    u32x4 w[2][kSmallSteps][3];
+    auto read_planes = [&](u32x4 (&v)[kSmallSteps][3], int slot) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) split_pair(w[u][2 * v], w[u][2 * v + 1], pl[0][v], pl[1][v], pl[2][v]);
+        for (int u = 0; u < kSmallSteps; ++u)
 #pragma unroll
-            for (int s = 2; s >= 0; --s) {   // lo, mid, hi: smaller terms first
-                const u32x4 wv = {pl[s][0], pl[s][1], pl[s][2], pl[s][3]};
+            for (int s = 2; s >= 0; --s) v[u][s] = planes[slot][u][s][lane];
+        __builtin_amdgcn_sched_barrier(0);   // on their way before the products that follow
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
-                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv),
-                                                                     __builtin_bit_cast(bf16x8, xv[u][i]), acc[i], 0, 0, 0);
+    for (int a = 0; a < AHEAD; ++a) load_x(xv[a], a);
+    stage_written();
+    read_planes(w[0], 0);
+    for (int st0 = 0; st0 < nst; st0 += AHEAD) {
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            const int st = st0 + a;
+            if (st >= nst) break;
+            if (st + 1 < nst) {
+                stage_written();
+                read_planes(w[(a + 1) & 1], (a + 1) & 1);
             }
+#pragma unroll
+            for (int u = 0; u < kSmallSteps; ++u)
+#pragma unroll
+                for (int s = 2; s >= 0; --s)   // lo, mid, hi: smaller terms first
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[a & 1][u][s]),
+                                                                  __builtin_bit_cast(bf16x8, xv[a][u]), acc, 0, 0, 0);
+            if (st + AHEAD < nst) load_x(xv[a], st + AHEAD);
         }
     }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) red[wave][i][lane] = acc[i];
-    __syncthreads();
-    if (wave >= MI) return;
-    f32x4 v = red[0][wave][lane];
-#pragma unroll
-    for (int q = 1; q < kWv; ++q) {
-        const f32x4 o = red[q][wave][lane];
-        v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
-    }
-    const int64_t t = t0 + wave * 16 + r;
     const int e = e0 + 4 * (lane >> 4);
     if (t >= S) return;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        if (e + q < E) logits[t * E + e + q] = v[q] + (bias != nullptr ? bias[e + q] : 0.f);
+        if (e + q < E) logits[t * E + e + q] = bias != nullptr ? acc[q] + bias[e + q] : acc[q];
 }
 
 template <int MI>
 static void launch_router_small(const moe_bf16* x, const float* Wr, const float* bias, int64_t S, int D, int E,
                                 float* logits, dim3 g, hipStream_t st) {
-    if (D <= 8 * 32)   // one step a wave
-        hipLaunchKernelGGL((router_small_kernel<MI, 1>), g, dim3(512), 0, st, x, Wr, bias, S, D, E, logits);
+    const dim3 b((kSmallSteps + MI) * 64);
+    // no more stages ahead than D has (loads past it return zero, and cost up to 1 us)
+    if (D <= 2 * 32 * kSmallSteps)
+        hipLaunchKernelGGL((router_small_kernel<MI, 2>), g, b, 0, st, x, Wr, bias, S, D, E, logits);
+    else if (D <= 4 * 32 * kSmallSteps)
+        hipLaunchKernelGGL((router_small_kernel<MI, 4>), g, b, 0, st, x, Wr, bias, S, D, E, logits);
     else
-        hipLaunchKernelGGL((router_small_kernel<MI, MI == 4 ? 2 : 4>), g, dim3(512), 0, st, x, Wr, bias, S, D, E, logits);
+        hipLaunchKernelGGL((router_small_kernel<MI, 8>), g, b, 0, st, x, Wr, bias, S, D, E, logits);
 }
 
 size_t router_ws_bytes(int D, int E) { return ((size_t)3 * E * D * 2 + 255) / 256 * 256; }
@@ -287,12 +333,12 @@ hipError_t launch_router_logits(const moe_bf16* x, const float* Wr, const float*
                                 int D, int E, float* logits, void* ws, hipStream_t st) {
     if (S == 0) return hipSuccess;
     // One launch while its workgroups fit the device at once, in the fewest
-    // tokens each that do (measured against split + tiles, their launch gap not
-    // counted, us): 64 tokens x 64 experts x D 2,048 6.8 / 13.8; 1,024 x 64 7.6 /
-    // 14.2; 2,048 x 64 (32 tokens a workgroup) 9.2 / 14.5; 4,096 x 64 (64) 12.8 / 16.9;
-    // 512 x 512 x 2,688 (64) 17.6 / 22.0; 512 x 8 x 256 3.4 / 6.0.  Past one round
-    // every workgroup's reading and splitting of the weights repeats: 8,192 x 64 x
-    // 2,048 22.0 / 17.1.
+    // tokens each that do (us, measured against split + tiles, their launch gap not
+    // counted): 64 tokens x 64 experts x D 2,048 8.2 / 15.2; 1,024 x 64 9.4 / 15.3;
+    // 2,048 x 64 (32 tokens a workgroup) 10.0 / 16.4; 4,096 x 64 (64) 13.8 / 16.4;
+    // 512 x 512 x 2,688 (64) 19.3 / 22.3; 512 x 8 x 256 3.1 / 6.7.  Past one round
+    // every workgroup's reading and splitting of the weights, a quarter to all of
+    // these times, repeats.
     for (int mi = 1; mi <= 4; mi *= 2) {
         const int64_t mt = (S + 16 * mi - 1) / (16 * mi), nt = (E + 15) / 16;
         if (mt * nt > cu_count()) continue;
