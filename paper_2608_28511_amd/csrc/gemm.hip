@@ -15,7 +15,7 @@
 // (v_mfma_f32_16x16x32_bf16):
 //   phased 256 x 256 (phased.h), 64 k per k tile: the dense weight gradients, and
 //     ROWS launches and the experts' weight gradients where its coarser tile
-//     count does not cost a round (take_phased).  Its two
+//     count does not cost a round (take_phased, launch_grouped_wgrad2).  Its two
 //     groups of waves alternate between reading fragments and multiplying, so
 //     the matrix pipes are busy 80-90% of the k loop (the 128-row tile: 67%);
 //     under it the chip is power bound: 1.6-1.75 GHz at 1.2-1.36 PFLOP/s.
@@ -24,7 +24,8 @@
 //   128 x 128, 4-stage ring of 32 KB stages, waves of 32 x 64 in a 4 x 2 grid:
 //     the smallest ROWS launches (rows_kind);
 //   256 x 256, 32 k per stage, 4-stage ring of 32 KB stages: the products over
-//     an MX-FP8 A that are long enough.
+//     an MX-FP8 A that are long enough, and the weight gradients of many experts
+//     with few rows each.
 // For all but the first neither the MFMAs nor copy bandwidth bound the kernel: all
 // eight waves read after each barrier and then all multiply, and the waits
 // are on LDS and copy latency.
@@ -1595,6 +1596,9 @@ hipError_t launch_grouped_rows_mx(const uint8_t* Aq, const uint8_t* A_scale, con
 }
 
 
+// Gradients that stay in the 256 MB last-level cache.
+constexpr int64_t kHeldBytes = (int64_t)220 << 20;
+
 // Both weight gradients of the expert FFN in one launch (gemm_kgrp2_kernel),
 // items of the experts with the most rows first.
 hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf16* B0, int64_t ldb0, float* C0,
@@ -1620,12 +1624,28 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
             items[h] += (int64_t)E * ((Ms[q] + kSchedBM[h] - 1) / kSchedBM[h]) * ((Ns[q] + BN - 1) / BN);
     }
     // The phased tile when its rounds of items over the device cost less, as in
-    // take_phased.  Measured, phased / 128-row: rounds 1 : 1 1.38 (32 items of 256
-    // rows), 1 : 2 0.85, 2 : 4 0.86-0.89, 4 : 8 0.83 (0.94-1.00 with 64 to 128 rows an
-    // expert, where the stores of the gradients take most of the time), 16 : 32
-    // 0.79-0.80, 32 : 64 of 32 rows an expert 0.94.
+    // take_phased, but not for fewer than two rounds or a k tile of rows an expert.
+    // Measured, phased / 128-row: rounds 1 : 2 0.82 on even loads, but 1.04 and 1.29
+    // where the loads vary as exp(0.7 z) or by Zipf's law, because the busiest
+    // expert's items, twice as long, are then the whole time; 2 : 4 0.86-0.90, 0.83
+    // and 1.0; 4 : 8 and more 0.80, 0.79 and 0.88.
+    // With fewer rows the stores take most of the time.  Where rows start on 64-byte
+    // pieces, one 256-row item a workgroup costs least (whole passes of forward
+    // and backward, 36 shapes: 0.96 of the 128-row tile's, phased 0.98; 184 experts x
+    // 24 rows, 1,120 x 3,168: the gradients 945 us, phased 993; below a round the
+    // 128-row tile: 7 experts x 22 rows, 416 x 416, 6.9 and 9.2).  Where they do not, and
+    // every 256-byte store covers parts of three cache lines, the more workgroups
+    // store at once the better: 128-row items (0.96 of phased, 256-row items 1.01), but
+    // for gradients that the last-level cache holds, whose cached stores the
+    // phased tile makes (0.98 of the 128-row tile's).
     const int64_t G = persistent_grid();
-    const bool tall = (items[1] + G - 1) / G * kPhasedRoundPct < (items[0] + G - 1) / G * 100;
+    const bool few = R < TileP::KD * (int64_t)E;
+    const bool on64 = ((ldc0 | ldc1 | c_stride0 | c_stride1) & 15) == 0 && (((uintptr_t)C0 | (uintptr_t)C1) & 63) == 0;
+    const bool held = (int64_t)E * (c_stride0 + c_stride1) * 4 <= kHeldBytes;
+    const bool phased = few ? !on64 && held && items[1] > G
+                            : items[1] >= 2 * G &&
+                                  (items[1] + G - 1) / G * kPhasedRoundPct < (items[0] + G - 1) / G * 100;
+    const bool tall = phased || (few ? on64 && items[1] >= G : items[1] >= 4 * G);
     for (int q = 0; q < 2; ++q) {
         a[q].m_tiles = (Ms[q] + kSchedBM[tall] - 1) / kSchedBM[tall];
         a[q].n_tiles = (Ns[q] + BN - 1) / BN;
@@ -1633,9 +1653,11 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
     const int64_t n_wg =
         kg_grid(E, (int64_t)a[0].m_tiles * a[0].n_tiles, (int64_t)a[1].m_tiles * a[1].n_tiles);
     if (n_wg > 0x7fffffff) return hipErrorInvalidConfiguration;
-    if (tall)
+    if (phased)
         hipLaunchKernelGGL(gemm_kgrp2_phased_kernel<false>, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0], a[1],
                            const_cast<int32_t*>(order) + order_claims(E), DensePlan{}, (float*)nullptr);
+    else if (tall)
+        hipLaunchKernelGGL(gemm_kgrp2_kernel<TileL>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a[0], a[1]);
     else
         hipLaunchKernelGGL(gemm_kgrp2_kernel<TileS>, dim3((unsigned)n_wg), dim3(kGemmThreads), 0, st, a[0], a[1]);
     return launch_check(st);

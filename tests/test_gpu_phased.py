@@ -108,15 +108,21 @@ def test_backward_products(D, F):
 WGRAD = [0, 1, 2, 63, 64, 65, 100, 127, 128, 129, 191, 192, 193, 0, 320, 7]
 
 
-@pytest.mark.parametrize("D,F", [(504, 512), (1000, 264), (760, 504)])
-@pytest.mark.parametrize("heavy", [0, 4000])
-def test_weight_gradients(D, F, heavy):
-    """Both weight gradients on the phased tile: short, empty and busy contractions, cut widths."""
-    counts = WGRAD * 4 + [heavy]
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    r = [_cdiv(len(counts) * sum(_cdiv(m, h) * _cdiv(n, 256) for m, n in ((F, D), (D, F))), cus) for h in (128, 256)]
-    if r[1] * 152 >= r[0] * 100:
-        pytest.skip("this device keeps 128-row tiles for the shape")
+def wgrad_kernel(counts, D, F):
+    """The pair launch's rule, restated."""
+    cus, E = torch.cuda.get_device_properties(0).multi_processor_count, len(counts)
+    items = [E * sum(_cdiv(m, h) * _cdiv(n, 256) for m, n in ((F, D), (D, F))) for h in (128, 256)]
+    r = [_cdiv(i, cus) for i in items]
+    if sum(counts) < 64 * E:
+        if D % 16 or F % 16:
+            return "phased" if items[1] > cus and E * D * F * 8 <= 220 << 20 else "small"
+        return "tall" if items[1] >= cus else "small"
+    if items[1] >= 2 * cus and r[1] * 152 < r[0] * 100:
+        return "phased"
+    return "tall" if items[1] >= 4 * cus else "small"
+
+
+def _check_wgrads(counts, D, F):
     g = torch.Generator(device=DEV).manual_seed(D * 1000 + F)
     R, E = sum(counts), len(counts)
     off = _segments(counts)
@@ -130,6 +136,26 @@ def test_weight_gradients(D, F, heavy):
         for e, (a, b) in enumerate(zip(o, o[1:])):
             assert torch.equal(dW1[e], x[a:b].float().T @ du[a:b].float()), e
             assert torch.equal(dW2[e], h[a:b].float().T @ dy[a:b].float()), e
+
+
+@pytest.mark.parametrize("D,F", [(504, 512), (1000, 264), (760, 504)])
+@pytest.mark.parametrize("heavy", [0, 4000])
+def test_weight_gradients(D, F, heavy):
+    """Both weight gradients on the phased tile: short, empty and busy contractions, cut widths."""
+    counts = WGRAD * 4 + [heavy or 100]
+    if wgrad_kernel(counts, D, F) != "phased":
+        pytest.skip("this device keeps 128-row tiles for the shape")
+    _check_wgrads(counts, D, F)
+
+
+# fewer than 64 rows an expert: by the rows' alignment, the items and the gradients' size
+@pytest.mark.parametrize("E,D,F,kernel", [(43, 528, 1040, "tall"), (90, 1008, 272, "tall"), (5, 528, 1040, "small"),
+                                          (43, 520, 1032, "phased"), (5, 520, 1032, "small"), (40, 1000, 904, "small")])
+def test_weight_gradients_of_few_rows(E, D, F, kernel):
+    counts = ([0, 1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 130] * 8)[:E]
+    if wgrad_kernel(counts, D, F) != kernel:
+        pytest.skip("the shape is for 256 compute units")
+    _check_wgrads(counts, D, F)
 
 
 @pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 1000, 5000])
