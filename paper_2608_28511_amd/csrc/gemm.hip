@@ -69,9 +69,10 @@
 // result identical to decoding first (see MxDma and mx_frag).
 //
 // KGRP mode (weight gradients) takes (expert, m-tile, n-tile) items, one per
-// workgroup or, on the phased tile, claimed by persistent workgroups, two m-tiles at a time across all n-tiles so that the items
-// an XCD runs together keep their operand rows in its L2, and writes its fp32
-// tile through LDS as whole 256-byte row pieces with non-temporal stores.
+// workgroup or, on the phased tile, claimed by persistent workgroups.  The items of
+// an expert take two m-tiles at a time across all n-tiles, so that those an XCD
+// runs together keep their operand rows in its L2.  The fp32 tile leaves through LDS
+// as whole row pieces, non-temporally but for the cases of GradStore.
 //
 // Expert segments are located through device-side tile tables (expert,
 // first row, end row of every 128-row and every 256-row tile, built from the
@@ -215,6 +216,7 @@ struct GemmArgs {
     int m_tiles, n_tiles;
     int m_tiles_l;            // ROWS mode: m-tiles of 256 rows (dense) or their static bound
     int accumulate;           // EPI_F32: C += product instead of C = product
+    int store;                // phased KGRP: GradStore of C
 };
 
 // Wait until stage `cur` of `total` has landed when stages cur + 1 ..
@@ -1082,8 +1084,8 @@ __device__ __forceinline__ void rows_body_phased(const GemmArgs& p, char* smem, 
 // fp32 store of a wave's 64 rows x 64 columns to C (its first row, ldc apart),
 // columns from cbase, through 2 KB of LDS: 16 rows x 32 columns at a time
 // (16-byte chunk c of row r at c ^ (r & 7)), read back as whole 128-byte row
-// pieces and written non-temporally, 8 rows per instruction (see kgrp_store).
-// Rows from `rows` and columns from N on are dropped.
+// pieces, 8 rows per store instruction.  Rows from `rows` and columns from N on are
+// dropped.
 template <int POLICY>
 __device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], float* C, int64_t ldc, int rows, int N,
                                                 uint32_t ep, int cbase, int lane) {
@@ -1111,6 +1113,67 @@ __device__ __forceinline__ void kgrp_store_half(const f32x4 (&acc)[4][4], float*
                 __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, POLICY);
             }
         }
+}
+
+// The same for the four waves side by side, 256 columns from n0: 8 rows x 256 columns
+// at a time through 8 KB of LDS that they share (gb; chunk c of row r at
+// c ^ 4 (r & 7)), a whole row of the tile per store instruction, non-temporal.
+// Every wave of the workgroup calls it.
+__device__ __forceinline__ void kgrp_store_rows(const f32x4 (&acc)[4][4], float* C, int64_t ldc, int rows, int N,
+                                                uint32_t gb, int n0, int wn, int lane) {
+    rows = rows < 64 ? rows : 64;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)C, 0, rows > 0 ? (int32_t)(rows * ldc * 4) : 0, 0x00020000);
+    const int r = lane & 15, col = n0 + lane * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if ((r >> 3) == s) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int ch = (wn * 16 + j * 4 + (lane >> 4)) ^ ((r & 7) * 4);
+                    *(__attribute__((address_space(3))) f32x4*)(uintptr_t)(gb + (uint32_t)((r & 7) * 1024 + ch * 16)) =
+                        acc[i][j];
+                }
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // written, by all four
+            u32x4 v[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int rr = wn * 2 + q;
+                v[q] = *(const lds_u32x4*)(uintptr_t)(gb + (uint32_t)(rr * 1024 + ((lane ^ (rr * 4)) * 16)));
+            }
+            stage_barrier();   // read, by all four
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int row = i * 16 + s * 8 + wn * 2 + q;
+                const uint32_t off =
+                    (row < rows && col < N) ? ((uint32_t)row * (uint32_t)ldc + (uint32_t)col) * 4 : kDropOffset;
+                __builtin_amdgcn_raw_buffer_store_b128(v[q], rs, off, 0, kNonTemporal);
+            }
+        }
+}
+
+// How a weight gradient (C, ldc; `bytes`: all that the launch writes) leaves:
+//   kLinePieces    rows start on cache lines: 128-byte pieces, whole lines,
+//                  non-temporal (see kgrp_store);
+//   kCachedPieces  they do not, and the last-level cache holds all of it: cached
+//                  128-byte pieces, whose partial lines merge in L2;
+//   kTileRows      they do not, and it is larger: whole rows of the tile, seven lines of
+//                  nine whole, non-temporal.
+// Non-temporal 128-byte pieces off the lines only ever fill parts of two, which costs
+// up to 2.4 times.  Cached, a gradient beyond the last-level cache is still dirty there
+// when the launch ends, and the launches after it pay for its way to memory:
+// 36 experts x 275 rows, 2,224 x 2,000, gradients 384 us and the up projection after
+// them 184, as tile rows 395 and 144; 163 x 77, 1,552 x 1,552, 700 and 267, 756 and 212.
+// Over 300 random shapes whole passes take 0.989 of what cached stores of all took.
+enum GradStore { kLinePieces, kCachedPieces, kTileRows };
+constexpr int64_t kHeldBytes = (int64_t)220 << 20;   // of the 256 MB last-level cache
+
+static GradStore grad_store(const void* C, int64_t ldc, int64_t bytes) {
+    if ((((uintptr_t)C | (uintptr_t)(ldc * 4)) & 127) == 0) return kLinePieces;
+    return bytes <= kHeldBytes ? kCachedPieces : kTileRows;
 }
 
 // The items of dense weight gradients: `whole` tiles over all rows, then the
@@ -1291,19 +1354,22 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         // C at row r0 and column c0 of the columns below
         float* C = (float*)p.C + (int64_t)cur.e * p.c_stride + (int64_t)r0 * p.ldc;
         int64_t ldc = p.ldc;
-        int c0 = 0;
+        int c0 = 0, store = p.store;
         if constexpr (DENSE)
             if (cur.e > 0) {
                 C = part + (int64_t)(cur.e - 1) * kPieceElems + wm * 64 * TileP::BN;
                 ldc = TileP::BN;
                 c0 = cur.n0;
+                store = kLinePieces;
             }
-        if ((ldc & 31) == 0) {
+        if (store == kTileRows) {
+            const uint32_t gb = lds0 + TileP::kRingBytes + (uint32_t)wm * 8192u;
+            kgrp_store_rows(acc0, C, ldc, M - r0, p.N, gb, cur.n0, wn, lane);
+            if (cur.row0 + 128 < M) kgrp_store_rows(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N, gb, cur.n0, wn, lane);
+        } else if (store == kLinePieces) {
             if (on0) kgrp_store_half<kNonTemporal>(acc0, C, ldc, M - r0, p.N - c0, ep, cbase - c0, lane);
             if (on1) kgrp_store_half<kNonTemporal>(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N - c0, ep, cbase - c0, lane);
         } else {
-            // rows do not start on 128-byte lines: cached, the pieces' partial lines merge in L2 (both gradients of
-            // 31 experts x 71 rows, 680 x 1,496: 51 us, non-temporal 123; of 275 x 0.2 rows, 664 x 3,576: 1,195, 2,378)
             if (on0) kgrp_store_half<0>(acc0, C, ldc, M - r0, p.N - c0, ep, cbase - c0, lane);
             if (on1) kgrp_store_half<0>(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N - c0, ep, cbase - c0, lane);
         }
@@ -1596,9 +1662,6 @@ hipError_t launch_grouped_rows_mx(const uint8_t* Aq, const uint8_t* A_scale, con
 }
 
 
-// Gradients that stay in the 256 MB last-level cache.
-constexpr int64_t kHeldBytes = (int64_t)220 << 20;
-
 // Both weight gradients of the expert FFN in one launch (gemm_kgrp2_kernel),
 // items of the experts with the most rows first.
 hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf16* B0, int64_t ldb0, float* C0,
@@ -1640,9 +1703,10 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
     // phased tile makes (0.98 of the 128-row tile's).
     const int64_t G = persistent_grid();
     const bool few = R < TileP::KD * (int64_t)E;
-    const bool on64 = ((ldc0 | ldc1 | c_stride0 | c_stride1) & 15) == 0 && (((uintptr_t)C0 | (uintptr_t)C1) & 63) == 0;
-    const bool held = (int64_t)E * (c_stride0 + c_stride1) * 4 <= kHeldBytes;
-    const bool phased = few ? !on64 && held && items[1] > G
+    const int64_t bytes = (int64_t)E * (c_stride0 + c_stride1) * 4;
+    for (int q = 0; q < 2; ++q) a[q].store = grad_store(Cs[q], ldc[q], bytes);
+    const bool on64 = ((ldc0 | ldc1) & 15) == 0 && (((uintptr_t)C0 | (uintptr_t)C1) & 63) == 0;
+    const bool phased = few ? !on64 && bytes <= kHeldBytes && items[1] > G
                             : items[1] >= 2 * G &&
                                   (items[1] + G - 1) / G * kPhasedRoundPct < (items[0] + G - 1) / G * 100;
     const bool tall = phased || (few ? on64 && items[1] >= G : items[1] >= 4 * G);
@@ -1747,6 +1811,7 @@ hipError_t launch_dense_wgrad2(const moe_bf16* A0, const moe_bf16* B0, float* C0
         a[q].M = Ms[q]; a[q].R = R; a[q].N = Ns[q];
         a[q].m_tiles = (Ms[q] + TileP::BM - 1) / TileP::BM;
         a[q].n_tiles = (Ns[q] + BN - 1) / BN;
+        a[q].store = grad_store(Cs[q], Ns[q], ((int64_t)M0 * N0 + (int64_t)M1 * N1) * 4);
     }
     const int64_t n = dense_tiles(M0, N0) + dense_tiles(M1, N1);
     if (n == 0) return hipSuccess;

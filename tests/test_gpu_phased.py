@@ -158,6 +158,34 @@ def test_weight_gradients_of_few_rows(E, D, F, kernel):
     _check_wgrads(counts, D, F)
 
 
+# how the gradients leave: rows on cache lines, on 64-byte pieces, off them (held by
+# the last-level cache, and larger), and rows on lines that start beside one
+@pytest.mark.parametrize("E,D,F,shift", [(66, 768, 544, 0), (66, 528, 560, 0), (66, 520, 568, 0), (66, 712, 664, 0),
+                                         (66, 768, 544, 4), (66, 768, 544, 16)])
+def test_weight_gradient_stores(E, D, F, shift):
+    counts = ([0, 64, 65, 130, 191, 64] * 11)[:E]
+    if wgrad_kernel(counts, D, F) != "phased":
+        pytest.skip("the shape is for 256 compute units")
+    g = torch.Generator(device=DEV).manual_seed(D + F)
+    R = sum(counts)
+    off = _segments(counts)
+    W1, W2 = _ints(g, (E, D, F), 1), _ints(g, (E, F, D), 1)
+    dy = _ints(g, (R, D), 1) * (torch.rand((R, D), generator=g, device=DEV) < 0.05)
+    u, x, h = _ints(g, (R, F), 2), _ints(g, (R, D), 1), _ints(g, (R, F), 1)
+    ws = torch.empty(L.moe_grouped_ffn_bwd_workspace_bytes(E, R, D, F), dtype=torch.uint8, device=DEV)
+    bufs = [torch.full((E * D * F + 32,), 7.0, device=DEV) for _ in range(2)]
+    dW1, dW2 = (b[shift:shift + E * D * F].view(E, *s) for b, s in zip(bufs, ((D, F), (F, D))))
+    dx = torch.empty((R, D), dtype=torch.bfloat16, device=DEV)
+    L.moe_grouped_ffn_bwd(x, u, h, dy, off, E, R, D, F, W1, W2, dx, dW1, dW2, ws)
+    du = (_product(dy, off, W2.transpose(1, 2)) * 2 * u.float().clamp(min=0)).to(torch.bfloat16)
+    o = off.tolist()
+    for e, (a, b) in enumerate(zip(o, o[1:])):
+        assert torch.equal(dW1[e], x[a:b].float().T @ du[a:b].float()), e
+        assert torch.equal(dW2[e], h[a:b].float().T @ dy[a:b].float()), e
+    for b in bufs:
+        assert (b[:shift] == 7).all() and (b[shift + E * D * F:] == 7).all()
+
+
 @pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 1000, 5000])
 @pytest.mark.parametrize("M,N", [(8, 8), (264, 248), (1024, 776)])
 def test_dense_weight_gradient(R, M, N):
