@@ -382,8 +382,10 @@ __device__ __forceinline__ int heavy_slots(const GemmArgs& p) {
     return h;
 }
 
-__device__ __forceinline__ KgItem kg_item(unsigned b, int E, int per0, int per1, int H) {
-    const int per = per0 + per1, perm = per0 > per1 ? per0 : per1;
+// heavy0, heavy1: the two problems' items in a heavy slot (per0 and per1, unless
+// those are cut smaller).
+__device__ __forceinline__ KgItem kg_item(unsigned b, int E, int per0, int per1, int H, int heavy0, int heavy1) {
+    const int per = heavy0 + heavy1, perm = per0 > per1 ? per0 : per1;
     const int64_t heavy = (int64_t)H * per;
     const int n_hc = (int)((heavy + kKgChunk - 1) / kKgChunk);
     const int x = (int)(b % kXcds), j = (int)(b / kXcds);
@@ -395,8 +397,8 @@ __device__ __forceinline__ KgItem kg_item(unsigned b, int E, int per0, int per1,
         if (g >= heavy) return it;
         it.r = (int)(g / per);
         const int rem = (int)(g - (int64_t)it.r * per);
-        it.q = rem >= per0 ? 1 : 0;
-        it.in = rem - it.q * per0;
+        it.q = rem >= heavy0 ? 1 : 0;
+        it.in = rem - it.q * heavy0;
         return it;
     }
     const int jj = j - nhx * kKgChunk, k = jj / perm;
@@ -408,14 +410,28 @@ __device__ __forceinline__ KgItem kg_item(unsigned b, int E, int per0, int per1,
 }
 
 // Items of XCD x in kg_item's order, its padding after the last one left out.
-__device__ __forceinline__ int kg_count(int x, int E, int per0, int per1, int H) {
+__device__ __forceinline__ int kg_count(int x, int E, int per0, int per1, int H, int heavy0, int heavy1) {
     const int perm = per0 > per1 ? per0 : per1;
-    const int n_hc = (int)(((int64_t)H * (per0 + per1) + kKgChunk - 1) / kKgChunk);
+    const int n_hc = (int)(((int64_t)H * (heavy0 + heavy1) + kKgChunk - 1) / kKgChunk);
     const int nhx = n_hc > x ? (n_hc - x + kXcds - 1) / kXcds : 0;
     const int xp = ((x - n_hc) % kXcds + kXcds) % kXcds;
     const int units = 2 * (E - H), full = units / kXcds;
     const int pos = (full & 1) ? kXcds - 1 - xp : xp;
     return nhx * kKgChunk + (full + (pos < units % kXcds ? 1 : 0)) * perm;
+}
+
+// Does the busiest expert's contraction, on the phased tile 1.35 us a k tile and
+// 10.5 an item, outlast a workgroup's share of the work, items_per_wg of every expert?
+// Halving the heavy items' rows costs about as much as it gains at 1.2 shares:
+// 6 and 14% lost at 1.05 and 1.2 (16 experts x 2,433 rows, 1,584 x 1,104; 7 x 2,321, 664 x
+// 3,328, all of them heavy), 7-20% won beyond.
+__device__ __forceinline__ bool outlasts(const GemmArgs& p, float items_per_wg) {
+    typedef const __attribute__((address_space(4))) int32_t* cptr;
+    int e = ((cptr)p.order)[0];
+    e = (e >= 0 && e < p.E) ? e : 0;
+    const float rows = (float)(((cptr)p.offsets)[e + 1] - ((cptr)p.offsets)[e]);
+    constexpr float kRow = 1.35f / 64, kItem = 10.5f;
+    return rows * kRow + kItem > 1.25f * ((float)p.R * kRow + (float)p.E * kItem) * items_per_wg;
 }
 
 // The pair launch's grid: every XCD's longest possible share (8 heavy slots).
@@ -431,7 +447,8 @@ inline int64_t kg_grid(int E, int64_t per0, int64_t per1) {
 template <class T>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_kernel(GemmArgs p0, GemmArgs p1) {
     __shared__ __attribute__((aligned(1024))) char smem[T::kRingBytes];
-    const KgItem it = kg_item(blockIdx.x, p0.E, p0.m_tiles * p0.n_tiles, p1.m_tiles * p1.n_tiles, heavy_slots(p0));
+    const int per0 = p0.m_tiles * p0.n_tiles, per1 = p1.m_tiles * p1.n_tiles;
+    const KgItem it = kg_item(blockIdx.x, p0.E, per0, per1, heavy_slots(p0), per0, per1);
     if (it.r < 0) return;
     const GemmArgs& p = it.q ? p1 : p0;
     const int eo = ((const __attribute__((address_space(4))) int32_t*)p0.order)[it.r];
@@ -1198,7 +1215,12 @@ static_assert(kKgSlotOff + 4 * 32 <= 160 * 1024, "LDS budget");
 // item's stores drain under the next one's first k tile.  The matrix pipes are
 // busy 72% of the launch at 24 experts x 4,779 rows (2,688 x 3,520), against
 // 79-83% of the row products: both operands take two LDS transpose reads a
-// fragment.  Measured there, this / one 256-row item a workgroup and one barrier
+// fragment.  Heavy slots (see kg_item) whose longest contraction would outlast
+// the device's even share of the work are taken in items of 128 rows, whose
+// second halves have no products (114 Zipf-loaded experts x 1,677 rows, 568 x 448,
+// 43,949 of them one expert's: 836 -> 684 us; 26 x 572, 800 x 1,008: 136 -> 113; over
+// 120 such launches whole passes take 0.99).
+// Measured, this / one 256-row item a workgroup and one barrier
 // a stage: 3,530 / 3,820 us; 128 Zipf-loaded experts x 1,024 rows (2,048 x
 // 1,024) 1,130-1,180 / 1,230.
 //
@@ -1219,14 +1241,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
     int32_t* const tab_k = tab_e + kKgMaxE;                   // first row,
     int32_t* const tab_n = tab_k + kKgMaxE;                   // row count
     struct Slot {
-        int q, e, k_begin, k_len, row0, n0;   // q < 0: no item; e < 0: padding of the order
+        int q, e, k_begin, k_len, row0, n0, bm;   // q < 0: no item; e < 0: padding of the order; bm: rows
     };
     Slot* const slots = (Slot*)(smem + kKgSlotOff);
 
     const int Gx = (int)gridDim.x / kXcds, x = (int)(blockIdx.x % kXcds), lx = (int)(blockIdx.x / kXcds);
     const int E = p0.E, R = (int)p0.R;
     const int per0 = p0.m_tiles * p0.n_tiles, per1 = p1.m_tiles * p1.n_tiles;
-    int H = 0, n_x = 0;
+    int H = 0, n_x = 0, heavy0 = per0, heavy1 = per1, bm_heavy = TileP::BM;
     if constexpr (!DENSE) {
         for (int r = tid; r < E; r += kGemmThreads) {
             int e = p0.order[r];
@@ -1239,21 +1261,27 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
             tab_n[r] = hi - lo;
         }
         H = heavy_slots(p0);
-        n_x = kg_count(x, E, per0, per1, H);
+        if (H > 0 && outlasts(p0, (float)(per0 + per1) / (float)gridDim.x)) {
+            bm_heavy = 128;
+            heavy0 = (int)(p0.M + 127) / 128 * p0.n_tiles;
+            heavy1 = (int)(p1.M + 127) / 128 * p1.n_tiles;
+        }
+        n_x = kg_count(x, E, per0, per1, H, heavy0, heavy1);
     }
-    // item `in` of problem q: two m-tiles at a time across all n-tiles
-    auto place = [&](Slot& s, int q, int in) {
-        const int n_tiles = q ? p1.n_tiles : p0.n_tiles, m_tiles = q ? p1.m_tiles : p0.m_tiles;
-        const int width = kKgM * n_tiles;
-        const int grp = in / width, first_m = grp * kKgM;
-        const int gsz = (m_tiles - first_m) < kKgM ? (m_tiles - first_m) : kKgM;
+    // item `in` of problem q, bm rows high: 512 rows at a time across all n-tiles
+    auto place = [&](Slot& s, int q, int in, int bm) {
+        const int n_tiles = q ? p1.n_tiles : p0.n_tiles, m_tiles = ((int)(q ? p1.M : p0.M) + bm - 1) / bm;
+        const int group = kKgM * TileP::BM / bm, width = group * n_tiles;
+        const int grp = in / width, first_m = grp * group;
+        const int gsz = (m_tiles - first_m) < group ? (m_tiles - first_m) : group;
         const int in2 = in - grp * width;
         s.q = q;
-        s.row0 = (first_m + in2 % gsz) * TileP::BM;
+        s.bm = bm;
+        s.row0 = (first_m + in2 % gsz) * bm;
         s.n0 = in2 / gsz * TileP::BN;
     };
     auto describe = [&](int j, int slot) {
-        Slot s{-1, -1, 0, 0, 0, 0};
+        Slot s{-1, -1, 0, 0, 0, 0, TileP::BM};
         if constexpr (DENSE) {
             const int g = j * (int)gridDim.x + x * Gx + lx;
             int in = g;
@@ -1266,15 +1294,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
                 s.k_begin = c * plan.chunk_rows < R ? c * plan.chunk_rows : R;
                 s.k_len = R - s.k_begin < plan.chunk_rows ? R - s.k_begin : plan.chunk_rows;
             }
-            if (g < plan.items) place(s, in >= per0 ? 1 : 0, in >= per0 ? in - per0 : in);
+            if (g < plan.items) place(s, in >= per0 ? 1 : 0, in >= per0 ? in - per0 : in, TileP::BM);
         } else if (j < n_x) {
-            const KgItem it = kg_item((unsigned)(j * kXcds + x), E, per0, per1, H);
+            const KgItem it = kg_item((unsigned)(j * kXcds + x), E, per0, per1, H, heavy0, heavy1);
             s.q = 0;
             if (it.r >= 0) {
                 s.e = tab_e[it.r];
                 s.k_begin = tab_k[it.r];
                 s.k_len = tab_n[it.r];
-                place(s, it.q, it.in);
+                place(s, it.q, it.in, it.r < H ? bm_heavy : TileP::BM);
             }
         }
         slots[slot] = s;
@@ -1292,6 +1320,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         u.k_len = __builtin_amdgcn_readfirstlane(s.k_len);
         u.row0 = __builtin_amdgcn_readfirstlane(s.row0);
         u.n0 = __builtin_amdgcn_readfirstlane(s.n0);
+        u.bm = __builtin_amdgcn_readfirstlane(s.bm);
         return u;
     };
     // at least two k tiles, so that the copies run at most one item ahead
@@ -1309,7 +1338,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         const int M = s.e < 0 ? 0 : (int)p.M;
         ph.da.rs = PH::DA::span(p.A, p.lda, s.row0, M, s.k_begin, s.k_begin + s.k_len);
         ph.db.rs = PH::DB::span(p.B, p.ldb, s.n0, p.N, s.k_begin, s.k_begin + s.k_len);
-        ph.da.first_chunks(p.lda, M - s.row0, wave, lane);
+        ph.da.first_chunks(p.lda, min(M - s.row0, s.bm), wave, lane);
         ph.db.first_chunks(p.ldb, p.N - s.n0, wave, lane);
         ph.nkd = k_tiles(s.k_len);
     };
@@ -1332,7 +1361,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         const GemmArgs& p = cur.q > 0 ? p1 : p0;
         const int M = cur.e < 0 ? 0 : (int)p.M;
         const int r0 = cur.row0 + wm * 64, cbase = cur.n0 + wn * 64;
-        const bool on0 = cbase < p.N && r0 < M, on1 = cbase < p.N && r0 + 128 < M;
+        const bool on0 = cbase < p.N && r0 < M;
+        const bool on1 = cur.bm > 128 && cbase < p.N && r0 + 128 < M;
         const int nk = k_tiles(cur.k_len);
         zero_acc(acc0);
         zero_acc(acc1);
@@ -1365,7 +1395,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         if (store == kTileRows) {
             const uint32_t gb = lds0 + TileP::kRingBytes + (uint32_t)wm * 8192u;
             kgrp_store_rows(acc0, C, ldc, M - r0, p.N, gb, cur.n0, wn, lane);
-            if (cur.row0 + 128 < M) kgrp_store_rows(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N, gb, cur.n0, wn, lane);
+            if (cur.bm > 128 && cur.row0 + 128 < M)
+                kgrp_store_rows(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N, gb, cur.n0, wn, lane);
         } else if (store == kLinePieces) {
             if (on0) kgrp_store_half<kNonTemporal>(acc0, C, ldc, M - r0, p.N - c0, ep, cbase - c0, lane);
             if (on1) kgrp_store_half<kNonTemporal>(acc1, C + 128 * ldc, ldc, M - r0 - 128, p.N - c0, ep, cbase - c0, lane);

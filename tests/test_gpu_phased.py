@@ -148,6 +148,19 @@ def test_weight_gradients(D, F, heavy):
     _check_wgrads(counts, D, F)
 
 
+# the pair launch's item lists: heavy experts only, some heavy ones among light ones
+# (whole items, and half-height ones where the busiest outlasts the rest), the
+# kernel's largest expert table
+@pytest.mark.parametrize("counts,D,F", [([250] * 8, 1032, 1800), ([700, 30, 600, 20, 650, 0, 500] + [40] * 9, 776, 1000),
+                                        ([3000, 64, 2000, 1500, 0, 900] + [65] * 10, 776, 1000),
+                                        ([0, 2500] + [70] * 30, 1000, 520), (WGRAD * 64, 520, 520)],
+                         ids=["all_heavy", "four_heavy", "half_height", "one_half_height", "1024_experts"])
+def test_weight_gradient_items(counts, D, F):
+    if wgrad_kernel(counts, D, F) != "phased":
+        pytest.skip("the shape is for 256 compute units")
+    _check_wgrads(counts, D, F)
+
+
 # fewer than 64 rows an expert: by the rows' alignment, the items and the gradients' size
 @pytest.mark.parametrize("E,D,F,kernel", [(43, 528, 1040, "tall"), (90, 1008, 272, "tall"), (5, 528, 1040, "small"),
                                           (43, 520, 1032, "phased"), (5, 520, 1032, "small"), (40, 1000, 904, "small")])
