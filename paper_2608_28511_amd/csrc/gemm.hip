@@ -1197,10 +1197,11 @@ static GradStore grad_store(const void* C, int64_t ldc, int64_t bytes) {
 // other tiles in `chunks` pieces of chunk_rows rows each (chunk-major, so that
 // what runs together shares operand rows), whose partial tiles tile_sum_kernel
 // adds in order.  items: all of them, pieces counted.
+// A partial tile has the rows and columns of the largest tile, not 256 of each.
 struct DensePlan {
     int whole, chunks, chunk_rows, items;
+    int piece_rows, piece_ld;
 };
-constexpr int kPieceElems = TileP::BM * TileP::BN;
 
 constexpr int kKgTabOff = TileP::kRingBytes + kWaves * 2048;
 constexpr int kKgMaxE = 1024;
@@ -1387,8 +1388,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
         int c0 = 0, store = p.store;
         if constexpr (DENSE)
             if (cur.e > 0) {
-                C = part + (int64_t)(cur.e - 1) * kPieceElems + wm * 64 * TileP::BN;
-                ldc = TileP::BN;
+                C = part + ((int64_t)(cur.e - 1) * plan.piece_rows + wm * 64) * plan.piece_ld;
+                ldc = plan.piece_ld;
                 c0 = cur.n0;
                 store = kLinePieces;
             }
@@ -1758,23 +1759,30 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
     return launch_check(st);
 }
 
-// The plan of dense weight gradients of n tiles over R rows on the 256
+// The plan of the dense weight gradients M0 x N0 and M1 x N1 over R rows on the 256
 // workgroups of a device (a device of another size runs the same plan, so the
 // sums' order is the same): whole rounds of tiles over all rows, then the rest
 // cut into the number of pieces whose rounds take least.  In units of one k
 // tile (1.5 us): a piece costs its k tiles and 4 more (start, stores, the
-// workgroups' spread), the sum of the pieces 0.035 per partial tile read or
-// written (256 KB at 5 TB/s) and 2 for its launch.  A chunk has at least two k tiles, and
-// the pieces' partial tiles at most 128 MB.
-static DensePlan dense_plan(int64_t R, int64_t n) {
+// workgroups' spread), the sum of the pieces 0.035 per 256 KB of partial tiles read or
+// written (5 TB/s) and 2 for its launch.  A chunk has at least two k tiles; there are
+// at most 64 chunks (of a single tile 64 leave a few us to win) and 128 MB of
+// partial tiles.
+static DensePlan dense_plan(int64_t R, int M0, int N0, int M1, int N1) {
     constexpr int64_t G = 256;
+    auto tiles = [](int M, int N) {
+        return (int64_t)((M + TileP::BM - 1) / TileP::BM) * ((N + TileP::BN - 1) / TileP::BN);
+    };
+    const int64_t n = tiles(M0, N0) + tiles(M1, N1);
     const int64_t nk = (R + TileP::KD - 1) / TileP::KD, tail = n % G;
-    DensePlan best{(int)(n - tail), 1, (int)R, (int)n};
+    const int rows = std::min(std::max(M0, M1), TileP::BM), cols = std::min(std::max(N0, N1), TileP::BN);
+    DensePlan best{(int)(n - tail), 1, (int)R, (int)n, rows, (cols + 31) / 32 * 32};   // rows of whole cache lines
+    const double piece = 0.035 * best.piece_rows * best.piece_ld / (TileP::BM * TileP::BN);
     double cost = 0;
-    for (int64_t c = 1; tail > 0 && (c == 1 || (tail * c <= 2 * G && 2 * c <= nk)); ++c) {
+    for (int64_t c = 1; tail > 0 && (c == 1 || (c <= 64 && tail * c <= 2 * G && 2 * c <= nk)); ++c) {
         const int64_t per = (nk + c - 1) / c;
         const double t = (double)((tail * c + G - 1) / G) * (double)(per + 4) +
-                         (c > 1 ? 0.035 * (double)(tail * (2 * c + 1)) + 2 : 0);
+                         (c > 1 ? piece * (double)(tail * (2 * c + 1)) + 2 : 0);
         if (c == 1 || t < cost) {
             cost = t;
             best.chunks = (int)c;
@@ -1785,13 +1793,9 @@ static DensePlan dense_plan(int64_t R, int64_t n) {
     return best;
 }
 
-static int64_t dense_tiles(int M, int N) {
-    return (int64_t)((M + TileP::BM - 1) / TileP::BM) * ((N + TileP::BN - 1) / TileP::BN);
-}
-
 size_t dense_wgrad_ws_bytes(int64_t R, int M0, int N0, int M1, int N1) {
-    const DensePlan pl = dense_plan(R, dense_tiles(M0, N0) + dense_tiles(M1, N1));
-    return pl.chunks > 1 ? (size_t)(pl.items - pl.whole) * kPieceElems * 4 : 0;
+    const DensePlan pl = dense_plan(R, M0, N0, M1, N1);
+    return pl.chunks > 1 ? (size_t)(pl.items - pl.whole) * pl.piece_rows * pl.piece_ld * 4 : 0;
 }
 
 // C tiles from `whole` on = the sum of their partial tiles, chunks ascending.
@@ -1799,7 +1803,8 @@ size_t dense_wgrad_ws_bytes(int64_t R, int M0, int N0, int M1, int N1) {
 __global__ __launch_bounds__(256) void tile_sum_kernel(GemmArgs p0, GemmArgs p1, DensePlan plan,
                                                        const float* __restrict__ part) {
     int in = plan.whole + (int)blockIdx.y;
-    const float* src = part + (int64_t)blockIdx.y * plan.chunks * kPieceElems;
+    const int64_t piece = (int64_t)plan.piece_rows * plan.piece_ld;
+    const float* src = part + (int64_t)blockIdx.y * plan.chunks * piece;
     const int per0 = p0.m_tiles * p0.n_tiles;
     const GemmArgs& p = in >= per0 ? p1 : p0;
     if (in >= per0) in -= per0;
@@ -1810,11 +1815,11 @@ __global__ __launch_bounds__(256) void tile_sum_kernel(GemmArgs p0, GemmArgs p1,
     const int row = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6), col = ((int)threadIdx.x & 63) * 4;
     const int m = (first_m + in2 % gsz) * TileP::BM + row, n = in2 / gsz * TileP::BN + col;
     if (m >= p.M || n >= p.N) return;
-    src += row * TileP::BN + col;
+    src += row * plan.piece_ld + col;
     f32x4 s = *(const f32x4*)src;
 #pragma unroll 4
     for (int c = 1; c < plan.chunks; ++c) {
-        const f32x4 v = *(const f32x4*)(src + (int64_t)c * kPieceElems);
+        const f32x4 v = *(const f32x4*)(src + c * piece);
         s[0] += v[0]; s[1] += v[1]; s[2] += v[2]; s[3] += v[3];
     }
     float* dst = (float*)p.C + (int64_t)m * p.ldc + n;   // 4-byte aligned
@@ -1844,15 +1849,14 @@ hipError_t launch_dense_wgrad2(const moe_bf16* A0, const moe_bf16* B0, float* C0
         a[q].n_tiles = (Ns[q] + BN - 1) / BN;
         a[q].store = grad_store(Cs[q], Ns[q], ((int64_t)M0 * N0 + (int64_t)M1 * N1) * 4);
     }
-    const int64_t n = dense_tiles(M0, N0) + dense_tiles(M1, N1);
-    if (n == 0) return hipSuccess;
-    const DensePlan pl = dense_plan(R, n);
+    const DensePlan pl = dense_plan(R, M0, N0, M1, N1);
+    if (pl.items == 0) return hipSuccess;
     const int64_t G = std::min<int64_t>(persistent_grid(), (pl.items + kXcds - 1) / kXcds * kXcds);
     hipLaunchKernelGGL(gemm_kgrp2_phased_kernel<true>, dim3((unsigned)G), dim3(kGemmThreads), 0, st, a[0], a[1],
                        (int32_t*)nullptr, pl, (float*)ws);
     hipError_t err = launch_check(st);
     if (err != hipSuccess || pl.chunks == 1) return err;
-    hipLaunchKernelGGL(tile_sum_kernel, dim3(TileP::BM / 4, (unsigned)(n - pl.whole)), dim3(256), 0, st, a[0], a[1], pl,
+    hipLaunchKernelGGL(tile_sum_kernel, dim3((unsigned)((pl.piece_rows + 3) / 4), (unsigned)((pl.items - pl.whole) / pl.chunks)), dim3(256), 0, st, a[0], a[1], pl,
                        (const float*)ws);
     return launch_check(st);
 }

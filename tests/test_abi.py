@@ -66,6 +66,11 @@ def test_workspace_queries(lib):
     assert lib.moe_router_logits_workspace_bytes(2044, 64) == 0   # D % 8
     assert lib.moe_router_logits_workspace_bytes(64, 0) == 0
     assert lib.moe_router_bwd_workspace_bytes(8192, 2048, 64) >= 8192 * 64 * 4 + 8192 * 192 * 2
+    # a dense gradient's partial tiles: at most 64, of its own size (rows padded to cache lines)
+    for S in (16384, 10 ** 6):
+        assert 0 < lib.moe_latent_proj_bwd_workspace_bytes(S, 8, 8) <= 64 * 8 * 32 * 4
+        assert lib.moe_latent_proj_bwd_workspace_bytes(S, 256, 24) <= 64 * 256 * 32 * 4
+        assert lib.moe_latent_proj_bwd_workspace_bytes(S, 4096, 1024) <= 128 << 20
     assert lib.moe_router_bwd_workspace_bytes(8192, 2044, 64) == 0
     assert lib.moe_latent_proj_bwd_workspace_bytes(16384, 4096, 1024) >= 4096 * 1024 * 4
     assert lib.moe_latent_proj_bwd_workspace_bytes(16384, 4096, 1020) == 0

@@ -199,8 +199,8 @@ def test_weight_gradient_stores(E, D, F, shift):
         assert (b[:shift] == 7).all() and (b[shift + E * D * F:] == 7).all()
 
 
-@pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 1000, 5000])
-@pytest.mark.parametrize("M,N", [(8, 8), (264, 248), (1024, 776)])
+@pytest.mark.parametrize("R", [0, 1, 64, 65, 130, 1000, 5000, 16384])
+@pytest.mark.parametrize("M,N", [(8, 8), (72, 40), (264, 248), (1024, 776)])
 def test_dense_weight_gradient(R, M, N):
     """Pieces of the contraction and their sum: none to 64 of them, the last ones short."""
     g = torch.Generator(device=DEV).manual_seed(R + M)
