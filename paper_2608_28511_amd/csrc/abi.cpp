@@ -14,7 +14,7 @@
 
 namespace {
 
-constexpr int kMaxE = 1024;
+constexpr int kMaxE = moe::kMaxExperts;
 constexpr int kMaxK = 32;
 constexpr int kMaxDim = 65536;
 constexpr int64_t kMaxRows = (int64_t)1 << 31;

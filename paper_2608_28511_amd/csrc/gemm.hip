@@ -1204,8 +1204,7 @@ struct DensePlan {
 };
 
 constexpr int kKgTabOff = TileP::kRingBytes + kWaves * 2048;
-constexpr int kKgMaxE = 1024;
-constexpr int kKgSlotOff = kKgTabOff + 3 * kKgMaxE * 4;
+constexpr int kKgSlotOff = kKgTabOff + 3 * kMaxExperts * 4;
 static_assert(kKgSlotOff + 4 * 32 <= 160 * 1024, "LDS budget");
 
 // The pair launch on the phased tile, one workgroup per CU that runs items of
@@ -1239,8 +1238,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_kgrp2_phased_kernel(Gemm
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
     const uint32_t ep = lds0 + TileP::kRingBytes + (uint32_t)wave * 2048u;
     int32_t* const tab_e = (int32_t*)(smem + kKgTabOff);      // per slot of the expert order: expert,
-    int32_t* const tab_k = tab_e + kKgMaxE;                   // first row,
-    int32_t* const tab_n = tab_k + kKgMaxE;                   // row count
+    int32_t* const tab_k = tab_e + kMaxExperts;                   // first row,
+    int32_t* const tab_n = tab_k + kMaxExperts;                   // row count
     struct Slot {
         int q, e, k_begin, k_len, row0, n0, bm;   // q < 0: no item; e < 0: padding of the order; bm: rows
     };
@@ -1703,7 +1702,7 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
                                  hipStream_t st) {
     if (R * (lda0 > ldb0 ? lda0 : ldb0) * 2 >= kMaxDmaBytes || R * (lda1 > ldb1 ? lda1 : ldb1) * 2 >= kMaxDmaBytes)
         return hipErrorInvalidValue;
-    if (order == nullptr || E < 1) return hipErrorInvalidValue;
+    if (order == nullptr || E < 1 || E > kMaxExperts) return hipErrorInvalidValue;
     GemmArgs a[2] = {};
     const moe_bf16* As[2] = {A0, A1};
     const moe_bf16* Bs[2] = {B0, B1};

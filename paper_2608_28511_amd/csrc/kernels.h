@@ -9,6 +9,9 @@
 
 namespace moe {
 
+// Experts of a layer: every kernel's per-expert tables in LDS hold this many.
+constexpr int kMaxExperts = 1024;
+
 enum { EPI_BF16 = 0, EPI_RELU2 = 1, EPI_DRELU2 = 2, EPI_F32 = 3 };
 
 // Compute units of the current device (read once per device).
