@@ -96,12 +96,11 @@ def parse():
 # scaled by what it reads for the plain 1 GiB device copy this script runs at
 # start-up (a copy reads and writes exactly 1 GiB).  The summary records a
 # digest of the GEMM sources; once they change, `traffic` is reported as null.
-GEMM_SOURCES = ("gemm.hip", "tile_dma.h", "kernels.h", "common.h")
-# The grouped GEMM's symbol carries its operand layout, epilogue and k-tail
-# flag (up: squared-ReLU epilogue; down: plain bf16); the tile height is
-# chosen inside the kernel.
-KERNEL_NAME = {"grouped_up": ("gemm_rows_kernel<false, 1, false>",),
-               "grouped_down": ("gemm_rows_kernel<false, 0, false>",),
+GEMM_SOURCES = ("gemm.hip", "phased.h", "tile_dma.h", "schedule.h", "kernels.h", "common.h")
+# The grouped GEMM's symbol carries its operand layout, epilogue, k-tail flag
+# (up: squared-ReLU epilogue; down: plain bf16) and the tile or tiles it holds.
+KERNEL_NAME = {"grouped_up": ("gemm_rows_kernel<false, 1, false,",),
+               "grouped_down": ("gemm_rows_kernel<false, 0, false,",),
                "grouped_up_mxfp8": ("gemm_rows_mx_kernel<1, false>",)}
 
 

@@ -55,3 +55,31 @@ def test_gemm_roofline_takes_the_bound_of_its_intensity():
     fl_b = 2.0 * base.R * base.D * base.F
     r = bench.gemm_roofline("grouped_up", fl_b, bench.gemm_bytes(base, base.E), 2e-4)
     assert r["bound"] == "mfma" and r["unit"] == "TFLOP/s" and abs(r["frac"] - r["mfma_frac"]) < 1e-9
+
+
+def test_traffic_digest_covers_the_gemm_sources():
+    """Every file that the grouped GEMM includes, so that no change leaves its counters looking current."""
+    import re
+    src = ROOT / "paper_2608_28511_amd" / "csrc"
+    seen, todo = set(), ["gemm.hip"]
+    while todo:
+        f = todo.pop()
+        if f not in seen and (src / f).exists():
+            seen.add(f)
+            todo += re.findall(r'#include "(\w+\.h)"', (src / f).read_text())
+    assert set(bench.GEMM_SOURCES) == seen
+
+
+def test_traffic_kernels_exist():
+    """The names that counter rows are matched by are those of the library's kernels."""
+    import shutil
+
+    import pytest
+
+    from paper_2608_28511_amd import _lib
+    if shutil.which("nm") is None or not _lib.LIB_PATH.exists():
+        pytest.skip("needs nm and the built library")
+    names = subprocess.run(["nm", "-C", str(_lib.LIB_PATH)], capture_output=True, text=True, check=True).stdout
+    names = [n.replace("__device_stub__", "") for n in names.splitlines()]
+    for k in bench.KERNEL_NAME:
+        assert any(bench.kernel_match(k, n) for n in names), k
