@@ -1421,12 +1421,14 @@ __host__ __device__ __forceinline__ int tile_rounds(int m_tiles, int n_tiles, in
 // The tile of a bf16 ROWS launch, from the m-tile counts of both heights
 // (every workgroup reads the same counts, so the whole grid takes the same
 // body): the phased 256-row tile when its rounds cost less than those of the
-// 128-row tile.  A phased round costs 1.3 (one round, the chip half idle) to
-// 1.6 (many rounds) of a 128-row one: measured against each other, phased /
-// 128-row, 2 : 1 rounds take 0.74-0.87 of the time, 5 : 3 0.90, 9 : 5 0.79, 3 : 2
-// 1.01-1.04, 1 : 1 1.02-1.3 (64 to 65,536 rows over 8 to 256 experts, and
-// dense products of 512 to 16,384 rows).
-constexpr int kPhasedRoundPct = 152;
+// 128-row tile.  Measured against each other (480 random loads of 6 to 300 experts,
+// 1,400 launches: geometric mean and range of phased / 128-row time, by the ratio of their
+// rounds): up to 2 rounds of 128-row tiles 1 : 2 0.83 (0.63-1.13), 1 : 1 1.18; 3 to 6
+// rounds 0.5 0.82, 0.6 0.87, 0.65 0.95 (0.78-1.12), 0.75 0.97 (0.81-1.18), 0.8 1.01, 1.0
+// 1.08; 7 and more 0.5 0.79, 0.6 0.86, 0.65 0.93, 0.7 0.92, 0.75 0.97, 1.0 1.02.  The
+// down projection of 256 uneven experts x 256 rows (2,688 -> 2,048), 14 : 21 rounds: 809-820
+// against 940 us.
+constexpr int kPhasedRoundPct = 130;
 __host__ __device__ __forceinline__ bool take_phased(int m_small, int m_tall, int n_tiles, int G) {
     return tile_rounds(m_tall, n_tiles, G) * kPhasedRoundPct < tile_rounds(m_small, n_tiles, G) * 100;
 }
@@ -1693,6 +1695,8 @@ hipError_t launch_grouped_rows_mx(const uint8_t* Aq, const uint8_t* A_scale, con
 }
 
 
+constexpr int kPhasedGradPct = 152;   // cost of a round of phased items, of one of 128-row items
+
 // Both weight gradients of the expert FFN in one launch (gemm_kgrp2_kernel),
 // items of the experts with the most rows first.
 hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf16* B0, int64_t ldb0, float* C0,
@@ -1739,7 +1743,7 @@ hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf1
     const bool on64 = ((ldc0 | ldc1) & 15) == 0 && (((uintptr_t)C0 | (uintptr_t)C1) & 63) == 0;
     const bool phased = few ? !on64 && bytes <= kHeldBytes && items[1] > G
                             : items[1] >= 2 * G &&
-                                  (items[1] + G - 1) / G * kPhasedRoundPct < (items[0] + G - 1) / G * 100;
+                                  (items[1] + G - 1) / G * kPhasedGradPct < (items[0] + G - 1) / G * 100;
     const bool tall = phased || (few ? on64 && items[1] >= G : items[1] >= 4 * G);
     for (int q = 0; q < 2; ++q) {
         a[q].m_tiles = (Ms[q] + kSchedBM[tall] - 1) / kSchedBM[tall];
