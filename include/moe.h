@@ -102,6 +102,8 @@ size_t moe_router_logits_workspace_bytes(int32_t D, int32_t E);
  * Each fp32 weight is used as the sum of three bf16 terms (its bf16
  * rounding and the bf16 roundings of the two successive remainders), which
  * equals it to within 2^-24 relative, so the logits carry fp32 accuracy.
+ * A token's logits depend on its own row, Wr and bias alone: they are the same,
+ * to the last bit, whether few or many tokens share the call.
  * Errors: MOE_ERR_SHAPE (S < 0, D not a multiple of 8 in [8, 65536], E not
  * in [1, 1024]), MOE_ERR_NULL / MOE_ERR_ALIGN for missing or misaligned
  * buffers, MOE_ERR_WORKSPACE for a missing or short ws. */

@@ -1551,9 +1551,10 @@ static int64_t narrow_grid(const GemmArgs& a) {
 // Expert segments, whose counts the host does not know: not with a single
 // round of 128-row tiles, and not below 80 rows per expert, where routing
 // without strong skew leaves no expert over 128 rows and both heights the same
-// tiles.  Such launches are short, and the kernel with both bodies costs them
-// up to 1 us (18.0 against 17.6 us at 1,024 rows of 8 experts, 43.8 against 43.0
-// us at 1,024 rows of 64).  The phased body needs two k tiles.
+// tiles (of 1,400 launches of random loads ten below it, with 26 to 75 rows an
+// expert, would have gained 2-15%).  Such launches are short, and the kernel with
+// both bodies costs them up to 1 us (18.0 against 17.6 us at 1,024 rows of 8
+// experts, 43.8 against 43.0 us at 1,024 rows of 64).  The phased body needs two k tiles.
 static RowsKind rows_kind(const GemmArgs& a, int64_t G) {
     if (narrow_grid(a) <= persistent_grid()) return kNarrow;
     if (a.Kd <= TileP::KD) return kWide;

@@ -117,8 +117,8 @@ hipError_t launch_dense_wgrad2(const moe_bf16* A0, const moe_bf16* B0, float* C0
                                const moe_bf16* B1, float* C1, int M1, int N1, int64_t R, void* ws, hipStream_t st);
 // Two KGRP products over the same expert segments in one launch (the expert
 // FFN's dW2 and dW1): the experts' items in `order` (required, from
-// launch_expert_order), the largest contractions first, dealt evenly to the
-// XCDs in chunks of consecutive items.
+// launch_expert_order), the largest contractions first, dealt to the XCDs and
+// there claimed by persistent workgroups or, with few rows or items, one a workgroup.
 hipError_t launch_grouped_wgrad2(const moe_bf16* A0, int64_t lda0, const moe_bf16* B0, int64_t ldb0, float* C0,
                                  int64_t ldc0, int64_t c_stride0, int M0, int N0, const moe_bf16* A1, int64_t lda1,
                                  const moe_bf16* B1, int64_t ldb1, float* C1, int64_t ldc1, int64_t c_stride1, int M1,

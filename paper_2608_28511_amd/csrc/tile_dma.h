@@ -244,11 +244,4 @@ __device__ __forceinline__ bf16x8 lds_tr_pair(uint32_t addr, uint32_t hi_off) {
     return __builtin_bit_cast(bf16x8, v);
 }
 
-__device__ __forceinline__ int xcd_remap(int pid, int n) {
-    const int q = n / kXcds, r = n % kXcds;
-    const int xcd = pid % kXcds, local = pid / kXcds;
-    return xcd < r ? xcd * (q + 1) + local : r * (q + 1) + (xcd - r) * q + local;
-}
-
-
 }  // namespace moe
