@@ -1425,10 +1425,12 @@ __host__ __device__ __forceinline__ int tile_rounds(int m_tiles, int n_tiles, in
 // 1,400 launches: geometric mean and range of phased / 128-row time, by the ratio of their
 // rounds): up to 2 rounds of 128-row tiles 1 : 2 0.83 (0.63-1.13), 1 : 1 1.18; 3 to 6
 // rounds 0.5 0.82, 0.6 0.87, 0.65 0.95 (0.78-1.12), 0.75 0.97 (0.81-1.18), 0.8 1.01, 1.0
-// 1.08; 7 and more 0.5 0.79, 0.6 0.86, 0.65 0.93, 0.7 0.92, 0.75 0.97, 1.0 1.02.  The
+// 1.08; 7 and more 0.5 0.79, 0.6 0.86, 0.65 0.93, 0.7 0.92, 0.75 0.97, 1.0 1.02.  Dense
+// rows (660 products of 512 to 16,384): 1 : 2 0.79, 2 : 4 0.78, 3 : 5 0.85, 2 : 3 0.95
+// (0.79-1.07), 3 : 4 1.06, which the line leaves out.  The
 // down projection of 256 uneven experts x 256 rows (2,688 -> 2,048), 14 : 21 rounds: 809-820
 // against 940 us.
-constexpr int kPhasedRoundPct = 130;
+constexpr int kPhasedRoundPct = 135;
 __host__ __device__ __forceinline__ bool take_phased(int m_small, int m_tall, int n_tiles, int G) {
     return tile_rounds(m_tall, n_tiles, G) * kPhasedRoundPct < tile_rounds(m_small, n_tiles, G) * 100;
 }

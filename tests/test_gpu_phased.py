@@ -26,12 +26,12 @@ def _cdiv(a, b):
 
 
 def phased(counts, N):
-    """The launch's rule, restated: rounds of the phased tile x 1.3 < rounds of the 128-row tile."""
+    """The launch's rule, restated: rounds of the phased tile x 1.35 < rounds of the 128-row tile."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     gx = cus // 8
     nt = _cdiv(N, 256)
     r = [_cdiv(_cdiv(sum(_cdiv(c, h) for c in counts), 8) * nt, gx) for h in (128, 256)]
-    return r[1] * 130 < r[0] * 100
+    return r[1] * 135 < r[0] * 100
 
 
 def _ints(g, shape, hi):
