@@ -38,15 +38,14 @@
 namespace moe {
 
 
-// Two weights' three bf16 terms, packed (the first in the low half).
+// Two weights' three bf16 terms, packed (the first in the low half): one
+// conversion per pair and term (converting one at a time made the waves that
+// split the chain of router_small_kernel: 64 tokens x 64 experts 8.2 us, now 7.7).
 __device__ __forceinline__ void split_pair(float w0, float w1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    const uint32_t h0 = f32_to_bf16(w0), h1 = f32_to_bf16(w1);
-    const float a0 = w0 - __uint_as_float(h0 << 16), a1 = w1 - __uint_as_float(h1 << 16);
-    const uint32_t m0 = f32_to_bf16(a0), m1 = f32_to_bf16(a1);
-    const uint32_t l0 = f32_to_bf16(a0 - __uint_as_float(m0 << 16)), l1 = f32_to_bf16(a1 - __uint_as_float(m1 << 16));
-    hi = h0 | (h1 << 16);
-    mid = m0 | (m1 << 16);
-    lo = l0 | (l1 << 16);
+    hi = pack_bf16x2(w0, w1);
+    const float a0 = w0 - bf16_lo(hi), a1 = w1 - bf16_hi(hi);
+    mid = pack_bf16x2(a0, a1);
+    lo = pack_bf16x2(a0 - bf16_lo(mid), a1 - bf16_hi(mid));
 }
 
 // ---- split: one lane per (expert, 8-wide d chunk) -------------------------
@@ -213,7 +212,7 @@ __global__ __launch_bounds__(TM / WM * (RE / WN) * 64, 1) void router_logits_ker
 // router_logits_kernel (32-wide d steps in order; lo, mid, hi), so a token's
 // logits do not depend, to the last bit, on how many tokens share its call.
 // That chain (192 dependent MFMAs at D = 2,048) is paid for: with D shared out to
-// eight waves and their sums added, 64 tokens x 64 experts took 6.8 us, not 8.2,
+// eight waves and their sums added, 64 tokens x 64 experts took 6.8 us, not 7.7,
 // but their last bits then changed with the size of the call.
 constexpr uint32_t kDropOffset = 0x80000000u;   // beyond any descriptor's range: reads as zero
 constexpr int kSmallSteps = 4;                  // d steps per stage, and waves that split
@@ -334,9 +333,9 @@ hipError_t launch_router_logits(const moe_bf16* x, const float* Wr, const float*
     if (S == 0) return hipSuccess;
     // One launch while its workgroups fit the device at once, in the fewest
     // tokens each that do (us, measured against split + tiles, their launch gap not
-    // counted): 64 tokens x 64 experts x D 2,048 8.2 / 15.2; 1,024 x 64 9.4 / 15.3;
-    // 2,048 x 64 (32 tokens a workgroup) 10.0 / 16.4; 4,096 x 64 (64) 13.8 / 16.4;
-    // 512 x 512 x 2,688 (64) 19.3 / 22.3; 512 x 8 x 256 3.1 / 6.7.  Past one round
+    // counted): 64 tokens x 64 experts x D 2,048 7.7 / 15.0; 1,024 x 64 8.7 / 16.0;
+    // 2,048 x 64 (32 tokens a workgroup) 9.9 / 15.7; 4,096 x 64 (64) 13.2 / 16.1;
+    // 512 x 512 x 2,688 (64) 19.1 / 22.0; 512 x 8 x 256 2.9 / 6.8.  Past one round
     // every workgroup's reading and splitting of the weights, a quarter to all of
     // these times, repeats.
     for (int mi = 1; mi <= 4; mi *= 2) {
