@@ -467,7 +467,9 @@ constexpr int kKgM = 2;
 // go there (16-byte chunk c of row r at c ^ r) and come back as whole
 // 256-byte row pieces, 4 rows per store instruction, written
 // non-temporally: the gradient is not read here, and full lines keep the
-// bypassing writes efficient while the operand rows stay in L2.
+// bypassing writes efficient while the operand rows stay in L2.  (Also where
+// rows start beside a line and a piece fills one of three: cached stores would
+// move the cost to the launches that follow, see GradStore.)
 template <int MI>
 __device__ __forceinline__ void kgrp_store(const f32x4 (&acc)[MI][4], const GemmArgs& p, int e, uint32_t ep, int rbase,
                                            int cbase, int lane) {
@@ -1213,13 +1215,13 @@ static_assert(kKgSlotOff + 4 * 32 <= 160 * 1024, "LDS budget");
 // of the next item start during the last two k tiles of the current one, so
 // neither a workgroup launch nor a cold pipeline stands between items, and an
 // item's stores drain under the next one's first k tile.  The matrix pipes are
-// busy 72% of the launch at 24 experts x 4,779 rows (2,688 x 3,520), against
-// 79-83% of the row products: both operands take two LDS transpose reads a
+// busy 71% of the launch at 24 experts x 4,779 rows (2,688 x 3,520), against
+// 74-78% of the row products: both operands take two LDS transpose reads a
 // fragment.  Heavy slots (see kg_item) whose longest contraction would outlast
 // the device's even share of the work are taken in items of 128 rows, whose
 // second halves have no products (114 Zipf-loaded experts x 1,677 rows, 568 x 448,
-// 43,949 of them one expert's: 836 -> 684 us; 26 x 572, 800 x 1,008: 136 -> 113; over
-// 120 such launches whole passes take 0.99).
+// 43,949 of them one expert's: 836 -> 684 us; 26 x 572, 800 x 1,008: 136 -> 113; whole
+// passes over 150 Zipf loads of two rounds and more take 0.985).
 // Measured, this / one 256-row item a workgroup and one barrier
 // a stage: 3,530 / 3,820 us; 128 Zipf-loaded experts x 1,024 rows (2,048 x
 // 1,024) 1,130-1,180 / 1,230.
